@@ -425,7 +425,10 @@ int32_t bddmp_solver_set_costs(bddmp_solver *s, const double *cost_dev);
  * of n iterations launches the first forward wave, then replays n - 1 times an iteration that ends
  * with the launch that also runs the next iteration's first forward wave, and once an iteration that
  * ends with the plain last backward wave: between calls the state is always that after whole
- * iterations. enable = 0: every wave is launched from the host. Both give bitwise the same results.
+ * iterations. Where the plan's components fit a workgroup's LDS (the grid MRFs, tracking instances,
+ * small problems), the iterations run as cell launches instead of replays: one or two launches per
+ * iteration, or many iterations per launch. enable = 0: every wave is launched from the host. All give
+ * bitwise the same results.
  */
 int32_t bddmp_solver_set_graphs(bddmp_solver *s, int32_t enable);
 
@@ -503,7 +506,7 @@ int32_t bddmp_solver_autotune(bddmp_solver *s, int32_t iters, int32_t *lanes);
  * launches they cover (one per wave) and the algorithmic bytes of those passes (20 bytes per node
  * and 8 per incidence: arcs 8, messages 12, multiplier 8; with fused_turn the last forward wave's
  * launch and bytes count with the backward pass that runs them); then the same number of iterations as
- * bddmp_solver_iterate runs them (graph replays by default) for iter_ms. The solver advances by
+ * bddmp_solver_iterate runs them (cell launches or graph replays by default) for iter_ms. The solver advances by
  * 2*n_iters iterations. Synchronises.
  */
 int32_t bddmp_solver_time_kernels(bddmp_solver *s, int32_t n_iters, bddmp_kernel_times *out);

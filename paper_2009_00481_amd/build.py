@@ -14,8 +14,8 @@ OBJ = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("BDDMP_ARCH", "gfx950")
 
-HOST_SOURCES = ["primal.cpp", "builder.cpp", "plan.cpp", "capi.cpp"]
-HIP_SOURCES = ["kernels.hip", "smooth.hip", "split.hip", "solver.hip"]
+HOST_SOURCES = ["primal.cpp", "builder.cpp", "cells.cpp", "plan.cpp", "capi.cpp"]
+HIP_SOURCES = ["kernels.hip", "cells.hip", "smooth.hip", "split.hip", "solver.hip"]
 # packed fp32 instructions stay off in every device build
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang",
              "-packed-fp32-ops", "-Wall", "-Wno-unused-result"]
@@ -30,7 +30,7 @@ def _run(cmd):
     return r
 
 
-HOST_ONLY_SOURCES = ["primal.cpp", "builder.cpp", "plan.cpp", "capi.cpp", "solver_host_only.cpp"]
+HOST_ONLY_SOURCES = ["primal.cpp", "builder.cpp", "cells.cpp", "plan.cpp", "capi.cpp", "solver_host_only.cpp"]
 HOST_ONLY_LIB = os.path.join(HERE, "libbddmp_host_san.so")
 # the host-only test build under the CPU sanitizers (run with libasan preloaded; see README)
 SANITIZE_FLAGS = ["-g", "-O1", "-fno-omit-frame-pointer", "-fsanitize=address,undefined", "-fno-sanitize-recover=all"]

@@ -377,6 +377,10 @@ int32_t bddmp_plan_digest(const bddmp_plan *h, uint64_t *digest) {
   digest_add(d, P.bgm); digest_add(d, P.wave_f); digest_add(d, P.wave_b); digest_add(d, P.order); digest_add(d, P.rank);
   digest_add(d, P.cost); digest_add(d, P.inc_var); digest_add(d, P.var_group); digest_add(d, P.inst_row32);
   digest_add(d, P.inst_lb_const);
+  for (const bddmp::CellStage &c : P.cell) {
+    digest_add(d, c.rec); digest_add(d, c.work); digest_add(d, c.w0); digest_add(d, c.w1); digest_add(d, c.row);
+    digest_add(d, c.grec); digest_add(d, c.garc); digest_add(d, c.layer); digest_add(d, c.link); digest_add(d, c.term);
+  }
   *digest = d;
   return BDDMP_OK;
 }

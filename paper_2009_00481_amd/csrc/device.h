@@ -60,6 +60,15 @@ __device__ __forceinline__ float c16val(const float *__restrict__ mb, int cs, ui
   return c < kTop ? msg_ld<COH>(mb + cs + int(c)) : (c == kTop ? 0.0f : INFINITY);
 }
 
+// multiplier update of eq. "mma-update"; rows forcing the variable (infinite difference) absorb
+// the finite differences of the others
+__device__ __forceinline__ float updated(float lam0, float d, float share, int nf) {
+  return nf == 0 ? (lam0 - d) + share : (isinf(d) ? lam0 + share : lam0 - d);
+}
+
+// Bound term index of a root layer from its entry in D.parent.
+__device__ __forceinline__ int root_term(int up) { return kRootTerm0 - up; }
+
 // General record of a layer: own slot, child slot, own width, child width, base of the child
 // level's in-arc offsets (-1 without child level).
 struct GRec {

@@ -16,6 +16,9 @@ constexpr int32_t kMaxWidth = 0x7FFF;   // widest level the 16-bit child codes c
 constexpr int kTile = 256;              // layers per workgroup of the wave kernels
 constexpr int kBigMax = 4096;           // max rows of one variable (J_i) a wave kernel handles
 constexpr int kLbBlocks = 1024;         // fixed partial count of the deterministic fp64 reductions
+constexpr int kLbStage = 256; // fixed chunk count of the bound reduction
+constexpr int kLbStages = 2 * kLbBlocks / kLbStage;  // iterations whose chunk totals fit Dev::part
+constexpr int kLbFinal = 1024, kLbSmall = 16384;  // one-workgroup bound: its lanes, and its most terms
 constexpr int kCutsPerBlock = 4;        // wide cuts per workgroup of the copy-arc kernels (one wavefront each)
 
 // Control words of one pass's dataflow launch (uint32 offsets): generation of the last launch,
@@ -32,8 +35,6 @@ constexpr uint32_t kC2Bot = 2u, kC2Top = 3u;
 constexpr uint32_t kMetaWidthShift = 8, kMetaRootBit = 1u << 10, kMetaPosShift = 11, kMetaLenShift = 21;
 constexpr uint32_t kMetaField = 0x3FFu;
 
-// Bit 31 of a backward tile's end position: the tile holds a root level (contributes to the bound).
-constexpr uint32_t kTileRootBit = 0x80000000u;
 // Bits 29-30 of a tile's start position: width class of its widest general level (0: <= 8 nodes,
 // 1: <= 32, 2: <= 128, 3: wider), which selects the lanes per general layer. Positions stay
 // below 2^29.
@@ -58,6 +59,28 @@ bool gsel_code(int32_t lanes, uint32_t &code);
 bool parse_groups(const char *s, uint32_t &gsel);
 // In-arc codes of the pull-form forward step: source node index (15 bits) | arc label << 15.
 constexpr uint32_t kInArcHi = 0x8000u;
+
+// Cells (cells.cpp, cells.hip). A local layer's descriptors: h = area of its parent's link (bits 0-14)
+// | kCellCount; w0 = h | child layer << 16 (kCellPair: h of the variable's two layers in one word);
+// w1 = rows of its variable (bits 0-6, 0 for a pad), position among them (7-13), kCellGeneral,
+// kCellLast, and in bits 16-31 the arcs of a narrow layer or the record of a general one. Areas are
+// pairs of floats.
+constexpr uint32_t kCellCount = 1u << 15, kCellPosShift = 7, kCellGeneral = 1u << 14, kCellLast = 1u << 15;
+// row part: first (bits 0-12) and last (13-25) local layer, whether it starts at the row's root and
+// ends at its last level, and the values behind that level's virtual nodes 0 and 1 (0 if set, else
+// +inf)
+constexpr uint32_t kCellRowRoot = 1u << 26, kCellRowLast = 1u << 27, kCellRowTermX = 1u << 28, kCellRowTermY = 1u << 29;
+// chunk of a step: first layer, or variable of kCellPair (bits 0-12), their number (13-22), whether
+// every level is regular, all of them taking / counting, whether the chunk begins / ends its step, and
+// the most rows of a variable less one (bits 28-31, 15: 16 or more)
+constexpr uint32_t kCellRegular = 1u << 23, kCellTakes = 1u << 24, kCellCounts = 1u << 25;
+constexpr uint32_t kCellStepBegin = 1u << 26, kCellStepEnd = 1u << 27;
+// kernel variants: one layer per lane (narrow levels only, or any), one two-row variable per lane
+constexpr int kCellLayers = 0, kCellGen = 1, kCellPair = 2;
+// limits: rows of a variable (one wavefront), nodes of a level (a lane loops over them), layers of a
+// cell, bytes of LDS of a component (estimate) and of a cell
+constexpr int kCellMaxRows = 64, kCellMaxWidth = 8, kCellMaxLayers = 8188;
+constexpr int kCellLdsMax = 140 << 10, kCellLdsCap = 160 << 10;
 
 // Records bddmp_last_error's message and returns code.
 int32_t set_error(int32_t code, const std::string &msg);
@@ -96,9 +119,11 @@ struct ArenaLayout {
   size_t fgt, bgt, fgm, bgm;
   size_t fwd_tiles, bwd_tiles, bwd_list, fwd_big, bwd_big;
   size_t bdd_canon_off, cost, var_first, var_nj;
-  size_t d_fresh, mbuf, xbuf, part, lbpart, lb_hist, scal;
+  size_t d_fresh, mbuf, xbuf, part, root_e, cut_part, lb_hist, scal;
   size_t inst_row, inst_lb;
   size_t cuts, cut_slots, cut_live, cut_rb, cut_arc, mu_in, dfw, dbw, cut_e, inst_cut, inst_cut_idx, exit_rec;
+  size_t c_rec[2], c_work[2], c_w0[2], c_w1[2], c_row[2], c_grec[2], c_garc[2], c_layer[2], c_link[2], c_term[2];
+  size_t c_lam[2], c_in[2];
   size_t total;
 };
 
@@ -108,6 +133,24 @@ struct WaveRange {
   int32_t list;                  // backward pass: 1 if positions go through bwd_list
   bool narrow_only;              // every layer of the wave is narrow
   int64_t nodes, layers;         // work of the wave (for the byte model)
+};
+
+// The cells of one stage: programs of local layers (shared by cells of equal structure), and per
+// cell the storage layers and the row parts' links and bound terms.
+struct CellStage {
+  int32_t n_cells = 0, block = 64, lds = 0, kind = 0;  // workgroup lanes, bytes of LDS, kernel variant
+  int32_t bw = 2;                                      // floats of a boundary message (even)
+  // 16 per cell: layers, chunks, bases of w0 / w1 and work; base in cell order (lamc, layer), first
+  // global row part, areas, 0; row parts and their base, general layers and their base; arcs of those
+  // and their base; 0, 0
+  std::vector<int32_t> rec;
+  std::vector<uint32_t> work;           // chunks in forward order
+  std::vector<uint32_t> w0, w1, row;    // per local layer (w0 of kCellPair: per two), per row part
+  // 4 per general layer: first arc | child layer << 16, own | child width << 4 | parent layer << 16, area
+  // of its link, 0 (0xFFFF: no such layer in the cell)
+  std::vector<uint32_t> grec, garc;
+  std::vector<int32_t> layer;           // cell order: storage layer, -1 for a pad
+  std::vector<int32_t> link, term;      // per global row part: the partner's in the other stage, the bound term (-1: none)
 };
 
 struct Plan {
@@ -129,7 +172,9 @@ struct Plan {
   std::vector<double> cost;
   // host images of the device arrays (layers in forward-wave-major order)
   std::vector<uint32_t> meta;         // [I] meta word of each layer
-  std::vector<int32_t> child, parent; // [I] next / previous level of the same row, -1 at the ends
+  // [I] next / previous level of the same row, -1 at the ends; a row's root layer holds -2 - t in
+  // parent, t the index of the row's bound term (root layers numbered in storage order)
+  std::vector<int32_t> child, parent;
   std::vector<uint32_t> garcs;        // [S] lo | hi << 16 (16-bit codes) at every node slot
   // [4I] or empty: own slot, child slot, own width | child width << 16, base of the child level's
   // in-arc offsets in rbeg (-1 without child level)
@@ -160,7 +205,9 @@ struct Plan {
   // own slot of a layer (device code derives it the same way)
   std::vector<int64_t> own_slot, cslot; // [I] own-level slot and child-level slot
   int32_t hist_cap = 4096;
-  int64_t n_lbpart = 0;               // backward tiles (normal + big) = bound partials per sweep
+  int32_t n_root = 0;                 // rows with variables = root layers = bound terms per sweep
+  int32_t root_stride = 0;            // n_root rounded up to 4 (terms of one iteration in the ring)
+  int32_t root_ring = 1;              // iterations whose bound terms are kept at once (plans with cells)
   // instances: offsets of variables, rows and canonical incidences [n_inst + 1], and each
   // instance's constant bound term (sum of min(0, c_i) over its variables in no row)
   std::vector<int64_t> inst_var, inst_row, inst_inc;
@@ -229,6 +276,12 @@ struct Plan {
   uint32_t gsel = kDefaultGsel;
   int64_t tile_work = kTileWideWork;
   int64_t class_tiles[kWidthClasses] = {0, 0, 0, 0};
+  // cell launches (cells.cpp): 0 none; 1 every instance component in one workgroup; 2 two stages
+  // (A = a prefix of each instance's order, B = the rest)
+  int32_t cell_kind = 0, n_comp = 0;
+  std::vector<uint8_t> var_stage;  // [n] 0 = A, 1 = B
+  std::vector<int32_t> var_comp;   // [n] component of the variable in its stage, -1 without rows
+  CellStage cell[2];
   ArenaLayout lay{};
 };
 
@@ -237,6 +290,12 @@ int32_t primal_search(const Plan &P, const float *M, int32_t mode, int64_t max_d
                       int32_t *feasible, int64_t *implied);
 int32_t restrict_row(const Plan &P, int32_t row, int32_t n_fix, const int32_t *vars, const int8_t *vals,
                      uint8_t *alive, int32_t *lo, int32_t *hi, int32_t *feasible);
+// cells.cpp
+void choose_cells(const Problem &p, Plan &P, const std::vector<int64_t> &iptr, const std::vector<int32_t> &ilist,
+                  const std::vector<int32_t> &inc_row);
+bool build_cells(Plan &P, const std::vector<int64_t> &iptr, const std::vector<int32_t> &ilist,
+                 const std::vector<int32_t> &inc_row, const std::vector<int32_t> &ownw, const std::vector<int32_t> &childw);
+std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, const std::vector<int32_t> &childw);
 void greedy_colour_order(const Problem &p, std::vector<int32_t> &order);
 
 }  // namespace bddmp

@@ -17,9 +17,11 @@ constexpr int kExtract = 2;   // min-marginals to the outputs, then step with un
 constexpr int kTurn = 3;      // backward launch over the last forward wave's levels: the forward update,
                               // then the backward update and step (narrow-only, storage-order tiles)
 constexpr int kWrap = 4;      // forward launch over the first forward wave's levels (the rows' roots): the
-                              // last backward wave's update and bound partials, then the next
+                              // last backward wave's update and bound terms, then the next
                               // iteration's forward update and step
-constexpr int kLbStage = 256; // fixed chunk count of the bound reduction
+// D.parent of a root layer: kRootTerm0 - t with t the index of its row's bound term (-1: a root cut
+// off by a split, which has none)
+constexpr int kRootTerm0 = -2;
 constexpr uint32_t kFlat = 7; // gsel code of the node-parallel path for general layers
 
 // Pointers into the caller's arena (see ArenaLayout) and the per-call outputs.
@@ -42,10 +44,11 @@ struct Dev {
   const int32_t *var_first, *var_nj;
   float *d_fresh, *mbuf;
   int8_t *xbuf;
-  double *part, *lbpart;
+  double *part;
+  float *root_e;     // bound term E^j of each row with variables, in storage order of the root layers
+  double *cut_part;  // bound partials of the copy-arc kernels
   double *lb_hist, *scal;
   float *out0, *out1;
-  int32_t n_bwd_tiles;  // bound partials of big backward tiles start here
   const int32_t *inst_row;  // [n_inst + 1] first row of each instance
   double *inst_lb;          // [n_inst] per-instance bounds
   double *lbc;              // [2] bound constants of the variables in no row: min-plus, smoothed
@@ -72,9 +75,9 @@ struct Dev {
 
 // One wave: nt normal tiles from tile0 of the pass's tile list (dir kFwd / kBwd, mode as above).
 // narrow_only selects the variant without wide levels, list the backward index-list variant.
-// kWrap (dir kFwd, narrow-only, no list): bwd_tile0 is the first backward tile of the same levels.
+// kWrap: dir kFwd, narrow-only, no list.
 hipError_t launch_wave(int dir, int mode, bool narrow_only, bool list, int nt, int tile0, const Dev &D,
-                       hipStream_t s, int bwd_tile0 = 0);
+                       hipStream_t s);
 // Dataflow launch of one pass (update mode; plans without big tiles): the pass's tiles in ticket
 // order, each after the tiles it depends on (see pass_kernel in kernels.hip).
 struct PassArgs {
@@ -123,8 +126,10 @@ hipError_t launch_nonfinite(const Dev &D, const float *p, int64_t n, hipStream_t
 hipError_t launch_nonfinite(const Dev &D, const double *p, int64_t n, hipStream_t s);
 // Bound of the backward sweep just run into the history ring at the device counter's slot, then
 // the counter advances (no host-side argument changes between iterations, so graphs can replay it).
+// n > 1: the bounds of n iterations at once, their terms root_stride apart (n <= hist_cap, and n <=
+// kLbStages where the terms take more than one workgroup).
 // which: 0 adds the min-plus constant D.lbc[0], 1 the smoothed one D.lbc[1].
-hipError_t launch_lb(const Dev &D, int nparts, int which, hipStream_t s);
+hipError_t launch_lb(const Dev &D, int nroot, int ncut, int which, hipStream_t s, int n = 1, int root_stride = 0);
 hipError_t launch_set_counter(const Dev &D, long long value, hipStream_t s);
 // Per-instance bound of the last backward sweep (sum over the instance's rows of E^j, recomputed
 // from the messages and multipliers; instance k's constant term is added by the host).
@@ -132,13 +137,36 @@ hipError_t launch_instance_bounds(const Dev &D, int n_inst, hipStream_t s);
 hipError_t launch_residual(const Dev &D, int n, hipStream_t s);
 hipError_t launch_round(const Dev &D, int n, int m, hipStream_t s);
 
+// Cell launches (cells.hip): the workgroups of one stage, each running its cell's part of the passes.
+// prog: kCellFirst A forward; kCellTurn B forward, then backward; kCellWrap A backward, then the next
+// iteration's forward; kCellFinal A backward; kCellWhole n iterations of cells without a boundary.
+// first, all: the stage's first / last launch of a call (multipliers from / to storage order).
+constexpr int kCellFirst = 0, kCellTurn = 1, kCellWrap = 2, kCellFinal = 3, kCellWhole = 4;
+struct CellLaunch {
+  int prog, kind, n_cells, block, lds, first, all, n;
+};
+struct CellArgs {
+  const int4 *rec;
+  const uint32_t *work;
+  const uint32_t *w0, *w1, *row;
+  const uint4 *grec;
+  const uint32_t *garc;
+  const int32_t *layer, *link, *term;
+  float *lamc;       // multipliers in cell order
+  const float *in;   // messages coming in at this stage's row parts, bw floats each
+  float *out;        // the other stage's
+  float *root_e;     // bound terms of the launch's first iteration, root_stride apart for the next
+  int32_t root_stride, bw;
+};
+hipError_t launch_cells(const CellLaunch &c, const Dev &D, const CellArgs &A, hipStream_t s);
+
 // Sub-BDD split (split.hip): copy duals to zero; the forward and backward copy-arc updates of
 // Alg. "Parallel min-marginal averaging" (update = 0: only the cut roots' forward messages and the
-// bound partials, written at lbpart[part0 + block]); export / import of the copy state per live pair.
+// bound partials, one per workgroup into cut_part); export / import of the copy state per live pair.
 hipError_t launch_copy_init(const Dev &D, int n_cuts, hipStream_t s);
 // n_narrow: the leading narrow cuts (one lane each); the others run one wavefront each.
 hipError_t launch_copy_fwd(const Dev &D, int n_cuts, int n_narrow, hipStream_t s);
-hipError_t launch_copy_bwd(const Dev &D, int n_cuts, int n_narrow, int update, int part0, hipStream_t s);
+hipError_t launch_copy_bwd(const Dev &D, int n_cuts, int n_narrow, int update, hipStream_t s);
 hipError_t launch_copy_io(const Dev &D, int n_cuts, bool out, float *mu_bar, float *mu, float *dfw, float *dbw,
                           hipStream_t s);
 

@@ -25,12 +25,6 @@ namespace bddmp {
 
 namespace {
 
-// multiplier update of eq. "mma-update"; rows forcing the variable (infinite difference) absorb
-// the finite differences of the others
-__device__ __forceinline__ float updated(float lam0, float d, float share, int nf) {
-  return nf == 0 ? (lam0 - d) + share : (isinf(d) ? lam0 + share : lam0 - d);
-}
-
 // One layer's work split around the J_i sum: begin() computes the min-marginals, push() /
 // bstep() apply the new multiplier in the forward push or the backward step.
 //
@@ -142,23 +136,21 @@ struct Layer {
     }
   }
 
-  // a narrow root level's new backward message (the backward step's value at node 0) as a bound
-  // term, 0 on other levels
-  __device__ __forceinline__ double root_value(float lam1) const {
+  // the new backward message of a root level (the backward step's value at node 0) is its row's
+  // energy E^j; up is the layer's entry in D.parent (root_term of the row's bound term)
+  __device__ __forceinline__ void root_step(const Dev &D, float lam1, int up) const {
     const float n0 = fminf(c2val(meta & 3u, b), c2val((meta >> 2) & 3u, b) + lam1);
-    return (meta & kMetaRootBit) ? double(n0) : 0.0;
+    if (up <= kRootTerm0) D.root_e[root_term(up)] = n0;
   }
 
   // backward step of this level (Alg. "Backward BDD update step") with the updated multiplier,
-  // stored at the parent layer's child slots; returns the root's new backward message (E^j) on a
-  // root level, else 0
-  __device__ __forceinline__ double bstep(const Dev &D, float lam1) const {
-    float r = 0.0f;
+  // stored at the parent layer's child slots; a root level's new message goes to the bound terms
+  __device__ __forceinline__ void bstep(const Dev &D, float lam1) const {
     if (narrow()) {
       const float n0 = fminf(c2val(meta & 3u, b), c2val((meta >> 2) & 3u, b) + lam1);
       const float n1 = fminf(c2val((meta >> 4) & 3u, b), c2val((meta >> 6) & 3u, b) + lam1);
       if (tgt >= 0) msg_st2<COH>(D.mbc + 2 * tgt, make_float2(n0, n1));
-      r = n0;
+      else if (tgt <= kRootTerm0) D.root_e[root_term(tgt)] = n0;
     } else if (LOOP) {
       const GRec g = grec_of(D, L);
       const int ps = tgt >= 0 ? D.grec[tgt].y : -1;  // the parent layer's child slots
@@ -166,10 +158,9 @@ struct Layer {
         const uint32_t a = D.garcs[g.os + u];
         const float v = fminf(c16val(D.mbc, g.cs, a & 0xFFFFu), c16val(D.mbc, g.cs, a >> 16) + lam1);
         if (ps >= 0) D.mbc[ps + u] = v;
-        if (u == 0) r = v;
+        if (u == 0 && tgt <= kRootTerm0) D.root_e[root_term(tgt)] = v;
       }
     }
-    return (meta & kMetaRootBit) ? double(r) : 0.0;
   }
 };
 
@@ -329,8 +320,7 @@ struct WaveLds {
   alignas(16) float cb[NARROW_ONLY ? 1 : kFlatCap];
 };
 
-// One tile of a wave: tix indexes the pass's tile list (dir DIR), btix the backward tile of the same
-// levels (kWrap) or tix.
+// One tile of a wave: tix indexes the pass's tile list (dir DIR).
 // LIST: backward positions go through bwd_list (a wave that is not one contiguous layer range).
 // Narrow layers run one per lane. General layers (a level or its child level wider than 2) are
 // collected per tile and run either node-parallel over the whole tile (flat path) or by groups of
@@ -345,7 +335,7 @@ struct NoWait {
 };
 
 template <int DIR, int MODE, bool NARROW_ONLY, bool LIST, bool COH = false, class Wait = NoWait>
-__device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh, const int tix, const int btix,
+__device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh, const int tix,
                                           const uint32_t w0, const uint32_t end, const bool list = true,
                                           const Wait &wait = Wait{}) {
   // with a wait (a tile of a launch that also runs the tiles it depends on), the loads no tile of
@@ -368,11 +358,7 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
   float *const s_cb = sh.cb;
   float *const s_fu = s_cb;
   const int p0 = int(w0 & kTilePosMask);
-  // a backward tile's end carries bit 31 when the tile holds a root level
-  // kWrap: btix is the same levels' backward tile (its root flag and bound partials)
-  const bool roots = (DIR == kBwd && (end & kTileRootBit) != 0u) ||
-                     (MODE == kWrap && (uint32_t(D.bwd_tiles[2 * btix + 1]) & kTileRootBit) != 0u);
-  const int cnt = int(end & ~kTileRootBit) - p0;
+  const int cnt = int(end) - p0;
   const int s = int(threadIdx.x);
   const bool active = s < cnt;
 
@@ -398,8 +384,10 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
   uint4 gmp = make_uint4(0u, 0u, 0u, 0u);
   if constexpr (!NARROW_ONLY)
     if (map_lane) gmp = *reinterpret_cast<const uint4 *>((DIR == kFwd ? D.fgm : D.bgm) + gtr.x + 16 * s);
+  int up = -1;  // kWrap: the layer's entry in D.parent, which names its row's bound term
   if (active) {
     const int L = (DIR == kBwd && LIST && list) ? D.bwd_list[p0 + s] : p0 + s;
+    if constexpr (MODE == kWrap) up = D.parent[L];
     if (!NARROW_ONLY) {
       grec = D.grec[L];
       gnb = D.gnb[L];
@@ -625,12 +613,8 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
         lam1 = updated(lam1, d, s_share[h], s_nf[h]);
       }
       if constexpr (MODE == kWrap) {
-        if (round == 0 && roots) {
-          // the backward step at the roots with the updated multipliers: E^j of each row, summed per
-          // wavefront into the backward tile's bound partials
-          const double v = wave_sum(active ? ly.root_value(lam1) : 0.0);
-          if ((threadIdx.x & 63) == 0) D.lbpart[kTile / 64 * btix + (int(threadIdx.x) >> 6)] = v;
-        }
+        // the backward step at the roots with the updated multipliers: E^j of each row
+        if (round == 0 && active) ly.root_step(D, lam1, up);
       }
     }
     if (active) D.lam[ly.L] = lam1;
@@ -689,29 +673,19 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
   if (DIR == kFwd) {
     if (active && !gen) ly.push(D, lam1);
   } else {
-    double e = 0.0;
-    if (active && !gen) e = ly.bstep(D, lam1);
+    if (active && !gen) ly.bstep(D, lam1);
     if constexpr (!NARROW_ONLY)
-      if (gen && (ly.meta & kMetaRootBit)) e = double(s_g.e[myk]);
-    // bound partial per wavefront: a fixed-shape wavefront sum, only in tiles holding root levels
-    // (the branch is uniform over the workgroup); the partials of other tiles stay at the zero the
-    // solver's reset stored
-    if (roots) {
-      const double v = wave_sum(e);
-      if ((threadIdx.x & 63) == 0) D.lbpart[kTile / 64 * tix + (int(threadIdx.x) >> 6)] = v;
-    }
+      if (gen && ly.tgt <= kRootTerm0) D.root_e[root_term(ly.tgt)] = s_g.e[myk];
   }
 }
 
 // One wave: a workgroup per tile, tiles tile0 .. tile0 + gridDim.x - 1 (XCD-aware order).
 template <int DIR, int MODE, bool NARROW_ONLY, bool LIST>
-__global__ __launch_bounds__(kTile) void wave_kernel(const Dev D, const int tile0, const int bwd_tile0) {
+__global__ __launch_bounds__(kTile) void wave_kernel(const Dev D, const int tile0) {
   __shared__ WaveLds<NARROW_ONLY> sh;
-  const int k = xcd_tile(int(blockIdx.x), int(gridDim.x));
-  const int tix = tile0 + k;
+  const int tix = tile0 + xcd_tile(int(blockIdx.x), int(gridDim.x));
   const int32_t *tiles = DIR == kFwd ? D.fwd_tiles : D.bwd_tiles;
-  wave_tile<DIR, MODE, NARROW_ONLY, LIST>(D, sh, tix, MODE == kWrap ? bwd_tile0 + k : tix, uint32_t(tiles[2 * tix]),
-                                          uint32_t(tiles[2 * tix + 1]));
+  wave_tile<DIR, MODE, NARROW_ONLY, LIST>(D, sh, tix, uint32_t(tiles[2 * tix]), uint32_t(tiles[2 * tix + 1]));
 }
 
 // LDS of the dataflow pass kernel: the general layout when the plan has general layers (its narrow
@@ -848,11 +822,11 @@ void pass_kernel(const Dev D, const PassArgs A) {
       set_priority((info >> 2) & 3u);
       const DepWait dw{ra, rb, A.dep_list, A.flags, gen, A.spin_limit, A.ctl + kPassErr, true};
       if constexpr (NARROW_PLAN) {
-        wave_tile<DIR, kUpdate, true, DIR == kBwd, true>(D, sh, t, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
+        wave_tile<DIR, kUpdate, true, DIR == kBwd, true>(D, sh, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
       } else if (info & 1u) {
-        wave_tile<DIR, kUpdate, true, DIR == kBwd, true>(D, sh.n, t, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
+        wave_tile<DIR, kUpdate, true, DIR == kBwd, true>(D, sh.n, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
       } else {
-        wave_tile<DIR, kUpdate, false, DIR == kBwd, true>(D, sh.g, t, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
+        wave_tile<DIR, kUpdate, false, DIR == kBwd, true>(D, sh.g, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
       }
       // every lane's coherent message stores of the tile complete (vmcnt 0; expcnt and lgkmcnt at
       // their maximum) before one lane stores the tile's flag; the barrier also frees the LDS
@@ -907,11 +881,11 @@ void group_kernel(const Dev D, const GroupArgs A) {
   // the tile issues what no tile of this pass writes (and scans its widths) before it waits
   const DepWait dw{ra, rb, A.dep_list, A.flags, gen, A.spin_limit, A.ctl + kPassErr, t >= A.t_first};
   if constexpr (NARROW_PLAN) {
-    wave_tile<DIR, kUpdate, true, DIR == kBwd, true>(D, sh, t, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
+    wave_tile<DIR, kUpdate, true, DIR == kBwd, true>(D, sh, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
   } else if (info & 1u) {
-    wave_tile<DIR, kUpdate, true, DIR == kBwd, true>(D, sh.n, t, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
+    wave_tile<DIR, kUpdate, true, DIR == kBwd, true>(D, sh.n, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
   } else {
-    wave_tile<DIR, kUpdate, false, DIR == kBwd, true>(D, sh.g, t, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
+    wave_tile<DIR, kUpdate, false, DIR == kBwd, true>(D, sh.g, t, uint32_t(ra.x), uint32_t(ra.y), list, dw);
   }
   if (t < A.t_last) {
     __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -924,8 +898,8 @@ void group_kernel(const Dev D, const GroupArgs A) {
 // a = t0 + 2 * block and a + 1 (when inside the launch), lane s holding layer s of both, so that
 // both tiles' fixed loads, dependency polls and message loads are in flight together and a
 // workgroup keeps twice the loads of the one-tile form outstanding. Each layer's arithmetic is that
-// of the one-tile form (the same J_i sum order, update, forward push or backward step, bound
-// partials per tile and wavefront), so the results are bitwise the same.
+// of the one-tile form (the same J_i sum order, update, forward push or backward step), so the
+// results are bitwise the same.
 //
 // When tile a + 1 reads messages tile a writes (the two lie in consecutive waves, and a is then the
 // last of its ascending dependency list), the workgroup runs tile a, publishes it, then runs tile
@@ -956,7 +930,7 @@ void group_pair_kernel(const Dev D, const GroupArgs A) {
     for (int k = 0; k < 2; ++k) {
       const int t = ta + k;
       const DepWait dw{ra[k], rb[k], A.dep_list, A.flags, gen, A.spin_limit, A.ctl + kPassErr, t >= A.t_first};
-      wave_tile<DIR, kUpdate, true, DIR == kBwd, true>(D, sh, t, t, uint32_t(ra[k].x), uint32_t(ra[k].y),
+      wave_tile<DIR, kUpdate, true, DIR == kBwd, true>(D, sh, t, uint32_t(ra[k].x), uint32_t(ra[k].y),
                                                        (uint32_t(ra[k].z) & 2u) != 0u, dw);
       if (t < A.t_last) {
         __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -967,15 +941,14 @@ void group_pair_kernel(const Dev D, const GroupArgs A) {
     return;
   }
   Layer<DIR, true, false, true> ly[2];
-  bool act[2], roots[2];
+  bool act[2];
   int lay[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const uint32_t w0 = uint32_t(ra[k].x), end = uint32_t(ra[k].y);
     const int p0 = int(w0 & kTilePosMask);
     const bool real = k == 0 || two;
-    roots[k] = real && DIR == kBwd && (end & kTileRootBit) != 0u;
-    act[k] = real && s < int(end & ~kTileRootBit) - p0;
+    act[k] = real && s < int(end) - p0;
     // every lane loads (a lane past the tile's layers reads its first one and keeps nothing), so
     // no branch separates the two tiles' loads
     const int q = p0 + (act[k] ? s : 0);
@@ -1031,14 +1004,9 @@ void group_pair_kernel(const Dev D, const GroupArgs A) {
       lam1[k] = updated(lam1[k], d[k], p_share[k][h], p_nf[k][h]);
       D.lam[ly[k].L] = lam1[k];
     }
-    if (DIR == kFwd) {
-      if (act[k]) ly[k].push(D, lam1[k]);
-    } else {
-      const double e = act[k] ? ly[k].bstep(D, lam1[k]) : 0.0;
-      if (roots[k]) {
-        const double v = wave_sum(e);
-        if ((s & 63) == 0) D.lbpart[kTile / 64 * (ta + k) + (s >> 6)] = v;
-      }
+    if (act[k]) {
+      if (DIR == kFwd) ly[k].push(D, lam1[k]);
+      else ly[k].bstep(D, lam1[k]);
     }
   }
   if (ta < A.t_last) {
@@ -1057,7 +1025,6 @@ __global__ __launch_bounds__(kTile) void wave_big_kernel(const Dev D, const int 
   __shared__ float s_d[kBigMax];
   __shared__ float s_share;
   __shared__ int s_nf;
-  __shared__ double s_red[kTile / 64];
   const int32_t *big = DIR == kFwd ? D.fwd_big : D.bwd_big;
   const int b = big0 + int(blockIdx.x);
   const int p0 = big[2 * b];
@@ -1087,7 +1054,6 @@ __global__ __launch_bounds__(kTile) void wave_big_kernel(const Dev D, const int 
     }
     __syncthreads();
   }
-  double e = 0.0;
   for (int s = int(threadIdx.x); s < cnt; s += kTile) {
     Layer<DIR, false, true> ly;
     ly.begin(D, (DIR == kBwd && LIST) ? D.bwd_list[p0 + s] : p0 + s);
@@ -1097,11 +1063,7 @@ __global__ __launch_bounds__(kTile) void wave_big_kernel(const Dev D, const int 
       D.lam[ly.L] = lam1;
     }
     if (DIR == kFwd) ly.push(D, lam1);
-    else e += ly.bstep(D, lam1);
-  }
-  if (DIR == kBwd) {
-    const double t = block_sum(e, s_red);
-    if (threadIdx.x == 0) D.lbpart[kTile / 64 * D.n_bwd_tiles + b] = t;
+    else ly.bstep(D, lam1);
   }
 }
 
@@ -1146,35 +1108,68 @@ __global__ __launch_bounds__(256) void nonfinite_kernel(const Dev D, const T *p,
   if (bad) atomicOr(D.flag, 1u);
 }
 
-// LB = sum_j E^j (problem (D)) from the per-tile partials of the backward sweep: kLbStage blocks
-// each sum one fixed contiguous chunk, then one block sums the chunk totals; fixed order throughout
-__global__ __launch_bounds__(256) void lb_stage_kernel(const Dev D, int nparts) {
-  __shared__ double sh[4];
-  const int chunk = (nparts + kLbStage - 1) / kLbStage;
-  const int q0 = int(blockIdx.x) * chunk, q1 = min(nparts, q0 + chunk);
-  // four independent running sums per lane (loads in flight together), then combined in order
+// LB = sum_j E^j (problem (D)): the terms are the rows' energies, stored as floats in root order
+// by whichever launch ran their backward step, then the copy-arc kernels' partial sums. Summed in
+// fp64 in one fixed shape that depends on the number of terms alone, so that every launch form and
+// tiling of a plan gives the same bound bitwise.
+//
+// Terms up to kLbSmall take one workgroup of kLbFinal lanes (a launch less per iteration); more
+// take kLbStage workgroups, each over one contiguous chunk, then one workgroup over the chunk
+// totals. The line lies where one workgroup's loads (16 per lane) take about as long as a launch.
+__device__ __forceinline__ double lb_chunk(const float *e, int q0, int q1, int lanes) {
+  // chunks start at multiples of four terms: four terms per load, one running sum for each
   double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-  int q = q0 + int(threadIdx.x);
-  for (; q + 3 * 256 < q1; q += 4 * 256) {
-    a0 += D.lbpart[q];
-    a1 += D.lbpart[q + 256];
-    a2 += D.lbpart[q + 2 * 256];
-    a3 += D.lbpart[q + 3 * 256];
+  int q = q0 + 4 * int(threadIdx.x);
+#pragma unroll 4
+  for (; q + 3 < q1; q += 4 * lanes) {
+    const float4 v = *reinterpret_cast<const float4 *>(e + q);
+    a0 += double(v.x);
+    a1 += double(v.y);
+    a2 += double(v.z);
+    a3 += double(v.w);
   }
-  for (; q < q1; q += 256) a0 += D.lbpart[q];
-  const double s = block_sum((a0 + a1) + (a2 + a3), sh);
-  if (threadIdx.x == 0) D.part[blockIdx.x] = s;
+  for (; q < q1; ++q) a0 += double(e[q]);
+  return (a0 + a1) + (a2 + a3);
+}
+__device__ __forceinline__ int lb_chunk_len(int nroot) { return ((nroot + kLbStage - 1) / kLbStage + 3) & ~3; }
+
+// blockIdx.y (lb_stage_kernel), blockIdx.x (the others): the iteration among the launch's
+__global__ __launch_bounds__(256) void lb_stage_kernel(const Dev D, int nroot, int ncut, int stride) {
+  __shared__ double sh[4];
+  const int b = int(blockIdx.x);
+  const float *e = D.root_e + size_t(blockIdx.y) * size_t(stride);
+  const int chunk = lb_chunk_len(nroot), cchunk = (ncut + kLbStage - 1) / kLbStage;
+  double a = lb_chunk(e, b * chunk, min(nroot, (b + 1) * chunk), 256);
+  for (int q = b * cchunk + int(threadIdx.x); q < min(ncut, (b + 1) * cchunk); q += 256) a += D.cut_part[q];
+  const double s = block_sum(a, sh);
+  if (threadIdx.x == 0) D.part[int(blockIdx.y) * kLbStage + b] = s;
+}
+
+// the bound into the history; a launch over one iteration also advances the device counter
+__device__ __forceinline__ void lb_record(const Dev &D, double lb) {
+  const long long n = *D.hist_n;
+  D.lb_hist[(n + int(blockIdx.x)) % D.hist_cap] = lb;
+  if (gridDim.x == 1) *D.hist_n = n + 1;
 }
 
 __global__ __launch_bounds__(kLbStage) void lb_final_kernel(const Dev D, int which) {
   __shared__ double sh[kLbStage / 64];
-  const long long n = *D.hist_n;
   const double c = D.lbc[which];
-  const double s = block_sum(D.part[threadIdx.x], sh);
-  if (threadIdx.x == 0) {
-    D.lb_hist[n % D.hist_cap] = s + c;
-    *D.hist_n = n + 1;
-  }
+  const double s = block_sum(D.part[int(blockIdx.x) * kLbStage + int(threadIdx.x)], sh);
+  if (threadIdx.x == 0) lb_record(D, s + c);
+}
+
+__global__ __launch_bounds__(kLbFinal) void lb_small_kernel(const Dev D, int which, int nroot, int ncut, int stride) {
+  __shared__ double sh[kLbFinal / 64];
+  const double c = D.lbc[which];
+  double a = lb_chunk(D.root_e + size_t(blockIdx.x) * size_t(stride), 0, nroot, kLbFinal);
+  for (int q = int(threadIdx.x); q < ncut; q += kLbFinal) a += D.cut_part[q];
+  const double s = block_sum(a, sh);
+  if (threadIdx.x == 0) lb_record(D, s + c);
+}
+
+__global__ void advance_counter_kernel(const Dev D, int n) {
+  if (threadIdx.x == 0) *D.hist_n += n;
 }
 
 __global__ void set_counter_kernel(const Dev D, long long value) {
@@ -1337,30 +1332,30 @@ int blocks_for(int64_t count, int per) { return int((count + per - 1) / per); }
 template <int DIR, int MODE>
 static hipError_t wave_dispatch(bool narrow_only, bool list, int nt, int tile0, const Dev &D, hipStream_t s) {
   if (narrow_only && !list)
-    hipLaunchKernelGGL((wave_kernel<DIR, MODE, true, false>), dim3(nt), dim3(kTile), 0, s, D, tile0, 0);
+    hipLaunchKernelGGL((wave_kernel<DIR, MODE, true, false>), dim3(nt), dim3(kTile), 0, s, D, tile0);
   else if (narrow_only)
-    hipLaunchKernelGGL((wave_kernel<DIR, MODE, true, true>), dim3(nt), dim3(kTile), 0, s, D, tile0, 0);
+    hipLaunchKernelGGL((wave_kernel<DIR, MODE, true, true>), dim3(nt), dim3(kTile), 0, s, D, tile0);
   else if (!list)
-    hipLaunchKernelGGL((wave_kernel<DIR, MODE, false, false>), dim3(nt), dim3(kTile), 0, s, D, tile0, 0);
+    hipLaunchKernelGGL((wave_kernel<DIR, MODE, false, false>), dim3(nt), dim3(kTile), 0, s, D, tile0);
   else
-    hipLaunchKernelGGL((wave_kernel<DIR, MODE, false, true>), dim3(nt), dim3(kTile), 0, s, D, tile0, 0);
+    hipLaunchKernelGGL((wave_kernel<DIR, MODE, false, true>), dim3(nt), dim3(kTile), 0, s, D, tile0);
   return hipGetLastError();
 }
 
 hipError_t launch_wave(int dir, int mode, bool narrow_only, bool list, int nt, int tile0, const Dev &D,
-                       hipStream_t s, int bwd_tile0) {
+                       hipStream_t s) {
   if (dir == kFwd && mode == kUpdate) return wave_dispatch<kFwd, kUpdate>(narrow_only, false, nt, tile0, D, s);
   if (dir == kFwd && mode == kExtract) return wave_dispatch<kFwd, kExtract>(narrow_only, false, nt, tile0, D, s);
   if (dir == kBwd && mode == kUpdate) return wave_dispatch<kBwd, kUpdate>(narrow_only, list, nt, tile0, D, s);
   if (dir == kBwd && mode == kNoUpdate) return wave_dispatch<kBwd, kNoUpdate>(narrow_only, list, nt, tile0, D, s);
   if (dir == kBwd && mode == kTurn) {
     if (!narrow_only || list) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((wave_kernel<kBwd, kTurn, true, false>), dim3(nt), dim3(kTile), 0, s, D, tile0, 0);
+    hipLaunchKernelGGL((wave_kernel<kBwd, kTurn, true, false>), dim3(nt), dim3(kTile), 0, s, D, tile0);
     return hipGetLastError();
   }
   if (dir == kFwd && mode == kWrap) {
     if (!narrow_only || list) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((wave_kernel<kFwd, kWrap, true, false>), dim3(nt), dim3(kTile), 0, s, D, tile0, bwd_tile0);
+    hipLaunchKernelGGL((wave_kernel<kFwd, kWrap, true, false>), dim3(nt), dim3(kTile), 0, s, D, tile0);
     return hipGetLastError();
   }
   return hipErrorInvalidValue;
@@ -1476,11 +1471,22 @@ hipError_t launch_nonfinite(const Dev &D, const double *p, int64_t n, hipStream_
   return nonfinite_dispatch(D, p, n, s);
 }
 
-hipError_t launch_lb(const Dev &D, int nparts, int which, hipStream_t s) {
-  hipLaunchKernelGGL(lb_stage_kernel, dim3(kLbStage), dim3(256), 0, s, D, nparts);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(lb_final_kernel, dim3(1), dim3(kLbStage), 0, s, D, which);
+hipError_t launch_lb(const Dev &D, int nroot, int ncut, int which, hipStream_t s, int n, int stride) {
+  const bool small = nroot + ncut <= kLbSmall;
+  if (n < 1 || n > D.hist_cap || (!small && n > kLbStages) || (n > 1 && (stride < nroot || stride % 4 || ncut)))
+    return hipErrorInvalidValue;
+  hipError_t e = hipSuccess;
+  if (small) {
+    hipLaunchKernelGGL(lb_small_kernel, dim3(n), dim3(kLbFinal), 0, s, D, which, nroot, ncut, stride);
+  } else {
+    hipLaunchKernelGGL(lb_stage_kernel, dim3(kLbStage, n), dim3(256), 0, s, D, nroot, ncut, stride);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(lb_final_kernel, dim3(n), dim3(kLbStage), 0, s, D, which);
+  }
+  e = hipGetLastError();
+  if (e != hipSuccess || n == 1) return e;
+  hipLaunchKernelGGL(advance_counter_kernel, dim3(1), dim3(64), 0, s, D, n);
   return hipGetLastError();
 }
 

@@ -199,6 +199,7 @@ std::string validate_layout(const Plan &P, const std::vector<int32_t> &ownw, con
       return "child layer";
     const int32_t pl = P.parent[L];
     if ((pl < 0) != (level[L] == 0 || root_cut[L])) return "parent layer";
+    if ((pl <= -2) != (level[L] == 0) || pl < -1 - P.n_root) return "bound term";
     if (pl >= 0 && (pl >= I || P.child[pl] != L || childw[pl] != w)) return "parent layer";
     for (int32_t u = 0; u < w; ++u) {
       const uint32_t a = P.garcs[size_t(os + u)];
@@ -307,7 +308,7 @@ std::string validate_layout(const Plan &P, const std::vector<int32_t> &ownw, con
         for (int32_t t = big ? wr.big_begin : wr.tile_begin; t < (big ? wr.big_end : wr.tile_end); ++t) {
           const uint32_t w0 = uint32_t(tiles[2 * size_t(t)]);
           const int64_t p0 = big ? int64_t(w0) : int64_t(w0 & kTilePosMask);
-          const int64_t p1 = uint32_t(tiles[2 * size_t(t) + 1]) & ~kTileRootBit;
+          const int64_t p1 = tiles[2 * size_t(t) + 1];
           if (big && (p0 >> kTileClsShift)) return "big tile start";
           const int64_t cap = big ? kBigMax : kTile;
           if (p1 <= p0 || p1 - p0 > cap || p0 < 0 || p1 > I) return "tile bounds";
@@ -353,7 +354,7 @@ std::string validate_layout(const Plan &P, const std::vector<int32_t> &ownw, con
         for (int32_t t = wr.tile_begin; t < wr.tile_end; ++t) {
           if (((info[size_t(t)] >> 1) & 1u) != uint32_t(pass && wr.list)) return "tile info list bit";
           const int64_t p0 = uint32_t(tiles[2 * size_t(t)]) & kTilePosMask;
-          const int64_t p1 = uint32_t(tiles[2 * size_t(t) + 1]) & ~kTileRootBit;
+          const int64_t p1 = tiles[2 * size_t(t) + 1];
           for (int64_t q = p0; q < p1; ++q) tile_of[size_t((pass && wr.list) ? P.bwd_list[size_t(q)] : q)] = t;
         }
       for (const WaveRange &wr : waves)
@@ -364,7 +365,7 @@ std::string validate_layout(const Plan &P, const std::vector<int32_t> &ownw, con
             if (lst[size_t(q)] < 0 || lst[size_t(q)] >= t || (q > d0 && lst[size_t(q)] <= lst[size_t(q) - 1]))
               return "dependency tile not smaller than its waiter";
           const int64_t p0 = uint32_t(tiles[2 * size_t(t)]) & kTilePosMask;
-          const int64_t p1 = uint32_t(tiles[2 * size_t(t) + 1]) & ~kTileRootBit;
+          const int64_t p1 = tiles[2 * size_t(t) + 1];
           bool narrow = true;
           for (int64_t q = p0; q < p1; ++q) {
             const int64_t L = (pass && wr.list) ? P.bwd_list[size_t(q)] : q;
@@ -401,7 +402,7 @@ std::string validate_layout(const Plan &P, const std::vector<int32_t> &ownw, con
       for (const WaveRange &wr : waves)
         for (int32_t t = wr.tile_begin; t < wr.tile_end; ++t) {
           const int64_t p0 = uint32_t(tiles[2 * size_t(t)]) & kTilePosMask;
-          const int64_t p1 = uint32_t(tiles[2 * size_t(t) + 1]) & ~kTileRootBit;
+          const int64_t p1 = tiles[2 * size_t(t) + 1];
           for (int64_t q = p0; q < p1; ++q)
             if (P.var_group[size_t(P.layer_var[size_t((pass && wr.list) ? P.bwd_list[size_t(q)] : q)])] != tq[size_t(t)])
               return "tile spans groups";
@@ -444,7 +445,7 @@ std::string validate_layout(const Plan &P, const std::vector<int32_t> &ownw, con
     for (const WaveRange &wr : waves)
       for (int32_t t = wr.tile_begin; t < wr.tile_end; ++t) {
         const int64_t p0 = uint32_t(tiles[2 * size_t(t)]) & kTilePosMask;
-        const int64_t p1 = uint32_t(tiles[2 * size_t(t) + 1]) & ~kTileRootBit;
+        const int64_t p1 = tiles[2 * size_t(t) + 1];
         std::vector<int32_t> own, chl;
         int32_t k = 0;
         for (int64_t q = p0; q < p1; ++q) {
@@ -796,6 +797,8 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
     }
   }
 
+  choose_cells(p, P, iptr, ilist, inc_row);
+
   // Storage order. Each forward wave sorts its variables by group of instances, then by backward wave, then by the storage
   // position of their earliest parent layer (the previous level of one of their rows), ties and
   // parentless variables by processing order. A workgroup's layers then push to and read from
@@ -909,6 +912,9 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
     P.child[Lq] = child_layer[Lq];
     if (child_layer[Lq] >= 0) P.parent[child_layer[Lq]] = int32_t(Lq);
   }
+  P.n_root = 0;
+  for (int64_t Lq = 0; Lq < I; ++Lq)
+    if (level[Lq] == 0) P.parent[Lq] = -2 - P.n_root++;
   // each layer writes only its own arcs and meta word: on several threads, general layers counted
   // per chunk
   std::vector<int64_t> n_gen_chunk;
@@ -1007,6 +1013,10 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
       P.rin.push_back(kManyInArcs);
       if (P.rarc.size() >= size_t(INT32_MAX)) return set_error(BDDMP_BDD_TOO_LARGE, "too many in-arcs");
     }
+  }
+  if (P.cell_kind && !build_cells(P, iptr, ilist, inc_row, ownw, childw)) {
+    P.cell_kind = 0;
+    P.cell[0] = P.cell[1] = CellStage{};
   }
   // general-level work per variable (own plus child nodes of its general layers), for the tiler
   std::vector<int64_t> wwork(size_t(n), 0);
@@ -1117,18 +1127,6 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
     P.bwd_contiguous = P.bwd_contiguous && contig;
   }
   if (P.bwd_contiguous) P.bwd_list.clear();
-  // flag backward tiles holding a root level; bound partials: one per wavefront of a normal tile,
-  // one per big tile
-  for (const WaveRange &wr : P.bwd_waves)
-    for (int32_t t = wr.tile_begin; t < wr.tile_end; ++t) {
-      bool roots = false;
-      for (int64_t q = P.bwd_tiles[2 * size_t(t)]; q < P.bwd_tiles[2 * size_t(t) + 1]; ++q) {
-        const int64_t Lq = wr.list ? P.bwd_list[size_t(q)] : q;
-        roots = roots || level[Lq] == 0;
-      }
-      if (roots) P.bwd_tiles[2 * size_t(t) + 1] = int32_t(uint32_t(P.bwd_tiles[2 * size_t(t) + 1]) | kTileRootBit);
-    }
-  P.n_lbpart = int64_t(kTile / 64) * int64_t(P.bwd_tiles.size() / 2) + int64_t(P.bwd_big.size() / 2);
   // turnaround: a variable of the last forward wave is last in each of its rows, so its backward
   // wave is the first; when the first backward wave holds exactly those layers, tiled alike, the
   // backward pass's first step on them can follow the forward pass's last one inside one launch
@@ -1142,7 +1140,7 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
       const size_t f = 2 * size_t(F.tile_begin + k), b = 2 * size_t(Bw.tile_begin + k);
       const int64_t f0 = int64_t(uint32_t(P.fwd_tiles[f]) & kTilePosMask), f1 = P.fwd_tiles[f + 1];
       const int64_t b0 = int64_t(uint32_t(P.bwd_tiles[b]) & kTilePosMask);
-      const int64_t b1 = int64_t(uint32_t(P.bwd_tiles[b + 1]) & ~kTileRootBit);
+      const int64_t b1 = int64_t(P.bwd_tiles[b + 1]);
       same = f0 == b0 && f1 == b1;
       for (int64_t L = f0; same && L < f1; ++L) same = P.child[size_t(L)] < 0;
     }
@@ -1161,7 +1159,7 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
       const size_t f = 2 * size_t(F.tile_begin + k), b = 2 * size_t(Bw.tile_begin + k);
       const int64_t f0 = int64_t(uint32_t(P.fwd_tiles[f]) & kTilePosMask), f1 = P.fwd_tiles[f + 1];
       const int64_t b0 = int64_t(uint32_t(P.bwd_tiles[b]) & kTilePosMask);
-      const int64_t b1 = int64_t(uint32_t(P.bwd_tiles[b + 1]) & ~kTileRootBit);
+      const int64_t b1 = int64_t(P.bwd_tiles[b + 1]);
       same = f0 == b0 && f1 == b1;
       for (int64_t L = f0; same && L < f1; ++L) same = P.parent[size_t(L)] < 0;
     }
@@ -1174,7 +1172,7 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
     for (const WaveRange &wr : waves)
       for (int32_t t = wr.tile_begin; t < wr.tile_end; ++t) {
         int32_t mw = 0;
-        const int64_t p1 = int64_t(uint32_t(tiles[2 * size_t(t) + 1]) & ~kTileRootBit);
+        const int64_t p1 = int64_t(tiles[2 * size_t(t) + 1]);
         for (int64_t q = tiles[2 * size_t(t)]; q < p1; ++q) {
           const int64_t Lq = (pass && wr.list) ? P.bwd_list[size_t(q)] : q;
           if (((P.meta[Lq] >> kMetaWidthShift) & 3u) == 0u) mw = std::max({mw, ownw[Lq], childw[Lq]});
@@ -1200,7 +1198,7 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
         gt[2 * size_t(t)] = -1;
         gen.clear();
         const int64_t p0 = uint32_t(tiles[2 * size_t(t)]) & kTilePosMask;
-        const int64_t p1 = uint32_t(tiles[2 * size_t(t) + 1]) & ~kTileRootBit;
+        const int64_t p1 = tiles[2 * size_t(t) + 1];
         int64_t tw = 0, tc = 0;
         for (int64_t q = p0; q < p1; ++q) {
           const int64_t Lq = (pass && wr.list) ? P.bwd_list[size_t(q)] : q;
@@ -1245,8 +1243,7 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
       const size_t nt = tiles.size() / 2;
       auto layer_at = [&](const WaveRange &wr, int64_t q) { return (pass && wr.list) ? int64_t(P.bwd_list[size_t(q)]) : q; };
       auto span = [&](int32_t t) {
-        return std::make_pair(int64_t(uint32_t(tiles[2 * size_t(t)]) & kTilePosMask),
-                              int64_t(uint32_t(tiles[2 * size_t(t) + 1]) & ~kTileRootBit));
+        return std::make_pair(int64_t(uint32_t(tiles[2 * size_t(t)]) & kTilePosMask), int64_t(tiles[2 * size_t(t) + 1]));
       };
       for (const WaveRange &wr : waves)
         for (int32_t t = wr.tile_begin; t < wr.tile_end; ++t)
@@ -1418,7 +1415,15 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
   A.mbuf = take(4 * nn);
   A.xbuf = take(nn);
   A.part = take(8 * 2 * size_t(kLbBlocks));
-  A.lbpart = take(8 * size_t(P.n_lbpart + P.n_cut_parts + 1));
+  // cell launches sum the bounds of several iterations at once: their terms, up to 64 MB of them
+  P.root_stride = (P.n_root + 3) & ~3;
+  P.root_ring = 1;
+  if (P.cell_kind) {
+    const int32_t most = P.n_root <= kLbSmall ? 64 : kLbStages;
+    P.root_ring = std::max<int32_t>(1, std::min({most, P.hist_cap, int32_t((int64_t(1) << 24) / std::max(P.root_stride, 1))}));
+  }
+  A.root_e = take(4 * size_t(P.root_stride) * size_t(P.root_ring));
+  A.cut_part = take(8 * size_t(P.n_cut_parts));
   A.lb_hist = take(8 * size_t(P.hist_cap));
   A.scal = take(256);
   A.inst_row = take(4 * P.inst_row32.size());
@@ -1451,9 +1456,28 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
   A.fflag = take(4 * P.ftinfo.size());
   A.bflag = take(4 * P.btinfo.size());
   A.pctl = take(4 * 2 * size_t(kPassCtlWords));
+  for (int q = 0; q < 2; ++q) {
+    const CellStage &C = P.cell[q];
+    A.c_rec[q] = take(4 * C.rec.size());
+    A.c_work[q] = take(4 * C.work.size());
+    A.c_w0[q] = take(4 * C.w0.size());
+    A.c_w1[q] = take(4 * C.w1.size());
+    A.c_row[q] = take(4 * C.row.size());
+    A.c_grec[q] = take(4 * C.grec.size());
+    A.c_garc[q] = take(4 * C.garc.size());
+    A.c_layer[q] = take(4 * C.layer.size());
+    A.c_link[q] = take(4 * C.link.size());
+    A.c_term[q] = take(4 * C.term.size());
+    A.c_lam[q] = take(4 * C.layer.size());
+    A.c_in[q] = take(4 * C.link.size() * size_t(C.bw));
+  }
   A.total = off;
   const std::string bad = validate_layout(P, ownw, childw, level, exit_cut, root_cut);
   if (!bad.empty()) return set_error(BDDMP_INVALID_ARG, "internal layout check failed: " + bad);
+  if (P.cell_kind) {
+    const std::string cbad = validate_cells(P, ownw, childw);
+    if (!cbad.empty()) return set_error(BDDMP_INVALID_ARG, "internal layout check failed: " + cbad);
+  }
   return BDDMP_OK;
 }
 

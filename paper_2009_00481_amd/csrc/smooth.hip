@@ -138,8 +138,7 @@ __global__ __launch_bounds__(kTile) void smooth_wave_kernel(const Dev D, const S
   const int tix = tile0 + xcd_tile(int(blockIdx.x), int(gridDim.x));
   const int p0 = int(uint32_t(tiles[2 * tix]) & kTilePosMask);
   const uint32_t end = uint32_t(tiles[2 * tix + 1]);
-  const bool roots = DIR == kBwd && (end & kTileRootBit) != 0u;
-  const int cnt = int(end & ~kTileRootBit) - p0;
+  const int cnt = int(end) - p0;
   const int s = int(threadIdx.x);
   const bool active = s < cnt;
   const float alpha = A.alpha;
@@ -203,11 +202,7 @@ __global__ __launch_bounds__(kTile) void smooth_wave_kernel(const Dev D, const S
         }
       }
     }
-    const double e = (active && (meta & kMetaRootBit)) ? double(r) : 0.0;
-    if (roots) {
-      const double v = wave_sum(e);
-      if ((threadIdx.x & 63) == 0) D.lbpart[kTile / 64 * tix + (int(threadIdx.x) >> 6)] = v;
-    }
+    if (active && tgt <= kRootTerm0) D.root_e[root_term(tgt)] = r;
   }
 }
 
@@ -262,7 +257,7 @@ __global__ __launch_bounds__(kTile) void smooth_adjoint_kernel(const Dev D, cons
   const int tix = tile0 + xcd_tile(int(blockIdx.x), int(gridDim.x));
   const int p0 = int(uint32_t(tiles[2 * tix]) & kTilePosMask);
   const uint32_t end = uint32_t(tiles[2 * tix + 1]);
-  const int cnt = int(end & ~kTileRootBit) - p0;
+  const int cnt = int(end) - p0;
   const int s = int(threadIdx.x);
   const bool active = s < cnt;
   const float alpha = A.alpha;

@@ -9,6 +9,7 @@
 #include <initializer_list>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
@@ -54,6 +55,7 @@ struct Solver {
   int group_waves = 0;
   bool group_pairs = false;
   uint32_t group_spin = 0;
+  CellArgs cell[2]{};  // cell launches of stages A and B (plans with cells)
   ~Solver() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (gexec_wrap) (void)hipGraphExecDestroy(gexec_wrap);
@@ -98,6 +100,11 @@ int32_t pass_error(uint32_t err) {
 // wave-group launches have none
 bool use_turn(const Solver &S) { return S.plan->fuse_turn && !S.dataflow && !S.pipe && !S.group_waves; }
 bool use_wrap(const Solver &S) { return S.plan->fuse_wrap && !S.dataflow && !S.pipe && !S.group_waves; }
+
+// cell launches: the default launch form's replayed iterations on plans with cells
+int cell_kind(const Solver &S) {
+  return S.use_graph && !S.dataflow && !S.pipe && !S.group_waves ? S.plan->cell_kind : 0;
+}
 
 // NONFINITE unless every value of the device arrays (float or double, n each) is finite; checked on
 // the device, then the stream is synchronised to read the result.
@@ -233,7 +240,7 @@ int32_t run_pass(Solver &S, int dir, int mode, std::vector<EventPair> *ev, hipSt
     if (wrap && dir == kBwd && w + 1 == nw) {
       // same tiles as the first forward wave (the plan checked it), launched in forward numbering
       const WaveRange &f = P.fwd_waves.front();
-      if (int32_t rc = launched(launch_wave(kFwd, kWrap, true, false, nt, f.tile_begin, S.D, st, wr.tile_begin),
+      if (int32_t rc = launched(launch_wave(kFwd, kWrap, true, false, nt, f.tile_begin, S.D, st),
                                 "wave kernel (wrap-around)"))
         return rc;
       continue;
@@ -249,13 +256,13 @@ int32_t run_pass(Solver &S, int dir, int mode, std::vector<EventPair> *ev, hipSt
   return tm.stop(st, int(nw - w0));
 }
 
-// the bound of the backward sweep just run, from its per-tile partials, into the history slot the
+// the bound of the backward sweep just run, from its rows' energies, into the history slot the
 // device counter names (the caller advances the host count S.n_hist)
 int32_t enqueue_lb(Solver &S, std::vector<EventPair> *ev, hipStream_t st, int which = 0) {
   const Plan &P = *S.plan;
   Timer tm{ev};
   if (int32_t rc = tm.start(st, 2)) return rc;
-  if (int32_t rc = launched(launch_lb(S.D, int(P.n_lbpart + P.n_cut_parts), which, st), "bound reduction")) return rc;
+  if (int32_t rc = launched(launch_lb(S.D, P.n_root, int(P.n_cut_parts), which, st), "bound reduction")) return rc;
   return tm.stop(st, 1);
 }
 
@@ -263,7 +270,7 @@ int32_t enqueue_lb(Solver &S, std::vector<EventPair> *ev, hipStream_t st, int wh
 // with (update) or without the backward copy-arc update
 int32_t enqueue_copy_bwd(Solver &S, int update, hipStream_t st) {
   const Plan &P = *S.plan;
-  return launched(launch_copy_bwd(S.D, int(P.n_cuts), int(P.n_cut_narrow), update, int(P.n_lbpart), st),
+  return launched(launch_copy_bwd(S.D, int(P.n_cuts), int(P.n_cut_narrow), update, st),
                   "copy-arc update");
 }
 
@@ -272,6 +279,40 @@ int32_t initial_sweep(Solver &S) {
   if (int32_t rc = enqueue_copy_bwd(S, 0, S.stream)) return rc;
   if (int32_t rc = enqueue_lb(S, nullptr, S.stream)) return rc;
   S.n_hist++;
+  return BDDMP_OK;
+}
+
+// one launch of a stage's cells; first, all: its first / last of an iterate call
+// of n iterations; slot: where the launch's bound terms go in the ring
+int32_t run_cells(Solver &S, int stage, int prog, bool first, bool all, int n, int slot) {
+  const CellStage &C = S.plan->cell[stage];
+  const CellLaunch c{prog, C.kind, C.n_cells, C.block, C.lds, first, all, n};
+  CellArgs a = S.cell[stage];
+  a.root_e += size_t(slot) * size_t(a.root_stride);
+  return launched(launch_cells(c, S.D, a, S.stream), "cell kernel");
+}
+
+// n iterations by cell launches, the bounds summed once per ring of terms
+int32_t cell_iterations(Solver &S, int32_t n) {
+  const Plan &P = *S.plan;
+  for (int32_t t = 0; t < n;) {
+    const int32_t k = std::min(n - t, P.root_ring);
+    if (P.cell_kind == 1) {
+      if (int32_t rc = run_cells(S, 1, kCellWhole, true, true, k, 0)) return rc;
+    } else {
+      if (t == 0)
+        if (int32_t rc = run_cells(S, 0, kCellFirst, true, false, 1, 0)) return rc;
+      for (int32_t q = 0; q < k; ++q) {
+        const bool last = t + q + 1 == n;
+        if (int32_t rc = run_cells(S, 1, kCellTurn, t + q == 0, last, 1, q)) return rc;
+        if (int32_t rc = run_cells(S, 0, last ? kCellFinal : kCellWrap, false, last, 1, q)) return rc;
+      }
+    }
+    if (int32_t rc = launched(launch_lb(S.D, P.n_root, 0, 0, S.stream, k, P.root_stride), "bound reduction")) return rc;
+    S.n_hist += k;
+    S.iters += k;
+    t += k;
+  }
   return BDDMP_OK;
 }
 
@@ -383,11 +424,11 @@ int32_t solver_bind(const Plan &P, void *arena, size_t bytes, void *stream, Solv
   D.mbuf = reinterpret_cast<float *>(b + A.mbuf);
   D.xbuf = reinterpret_cast<int8_t *>(b + A.xbuf);
   D.part = reinterpret_cast<double *>(b + A.part);
-  D.lbpart = reinterpret_cast<double *>(b + A.lbpart);
+  D.root_e = reinterpret_cast<float *>(b + A.root_e);
+  D.cut_part = reinterpret_cast<double *>(b + A.cut_part);
   D.lb_hist = reinterpret_cast<double *>(b + A.lb_hist);
   D.scal = reinterpret_cast<double *>(b + A.scal);
   D.out0 = D.out1 = nullptr;
-  D.n_bwd_tiles = int32_t(P.bwd_tiles.size() / 2);
   D.hist_n = reinterpret_cast<long long *>(b + A.scal + 64);
   D.flag = reinterpret_cast<unsigned *>(b + A.scal + 128);
   D.lbc = reinterpret_cast<double *>(b + A.scal + 80);
@@ -411,6 +452,25 @@ int32_t solver_bind(const Plan &P, void *arena, size_t bytes, void *stream, Solv
   D.fgm = reinterpret_cast<const uint8_t *>(b + A.fgm);
   D.bgm = reinterpret_cast<const uint8_t *>(b + A.bgm);
   D.gamma = P.split_gamma;
+  for (int q = 0; q < 2; ++q) {
+    CellArgs &c = S->cell[q];
+    c.rec = reinterpret_cast<const int4 *>(b + A.c_rec[q]);
+    c.work = reinterpret_cast<const uint32_t *>(b + A.c_work[q]);
+    c.w0 = reinterpret_cast<const uint32_t *>(b + A.c_w0[q]);
+    c.w1 = reinterpret_cast<const uint32_t *>(b + A.c_w1[q]);
+    c.row = reinterpret_cast<const uint32_t *>(b + A.c_row[q]);
+    c.grec = reinterpret_cast<const uint4 *>(b + A.c_grec[q]);
+    c.garc = reinterpret_cast<const uint32_t *>(b + A.c_garc[q]);
+    c.layer = reinterpret_cast<const int32_t *>(b + A.c_layer[q]);
+    c.link = reinterpret_cast<const int32_t *>(b + A.c_link[q]);
+    c.term = reinterpret_cast<const int32_t *>(b + A.c_term[q]);
+    c.lamc = reinterpret_cast<float *>(b + A.c_lam[q]);
+    c.in = reinterpret_cast<const float *>(b + A.c_in[q]);
+    c.out = reinterpret_cast<float *>(b + A.c_in[1 - q]);
+    c.bw = P.cell[q].bw;
+    c.root_e = D.root_e;
+    c.root_stride = P.root_stride;
+  }
   for (int p = 0; p < 2; ++p) {
     PassArgs &pa = S->pass[p];
     pa.trec = reinterpret_cast<const int4 *>(b + (p ? A.btrec : A.ftrec));
@@ -474,11 +534,20 @@ int32_t solver_bind(const Plan &P, void *arena, size_t bytes, void *stream, Solv
       up(A.fgm, P.fgm.data(), P.fgm.size()),
       up(A.bgm, P.bgm.data(), P.bgm.size()),
   };
-  for (hipError_t e : errs)
-    if (e != hipSuccess) {
-      delete S;
-      return hip_fail(e, "hipMemcpyAsync (upload)");
-    }
+  for (int q = 0; q < 2; ++q) {
+    const CellStage &c = P.cell[q];
+    auto bytes = [](const auto &v) { return std::make_pair(static_cast<const void *>(v.data()), 4 * v.size()); };
+    const std::pair<size_t, std::pair<const void *, size_t>> arrays[] = {
+        {A.c_rec[q], bytes(c.rec)},     {A.c_work[q], bytes(c.work)},   {A.c_w0[q], bytes(c.w0)},
+        {A.c_w1[q], bytes(c.w1)},       {A.c_row[q], bytes(c.row)},     {A.c_grec[q], bytes(c.grec)},
+        {A.c_garc[q], bytes(c.garc)},   {A.c_layer[q], bytes(c.layer)}, {A.c_link[q], bytes(c.link)},
+        {A.c_term[q], bytes(c.term)}};
+    for (const auto &a : arrays)
+      if (const hipError_t e = up(a.first, a.second.first, a.second.second); e != hipSuccess) {
+        delete S;
+        return hip_fail(e, "hipMemcpyAsync (upload)");
+      }
+  }
   // dataflow launch state: flags and control words start at zero (generation 0, no launch yet)
   for (const auto &z : {std::make_pair(A.fflag, P.ftinfo.size()), std::make_pair(A.bflag, P.btinfo.size()),
                         std::make_pair(A.pctl, 2 * size_t(kPassCtlWords))})
@@ -506,9 +575,6 @@ int32_t solver_reset(Solver &S) {
   if (int32_t rc = launched(launch_init_lambda(S.D, int(P.I), S.stream), "init_lambda")) return rc;
   if (int32_t rc = launched(launch_root_zero(S.D, P.m, S.stream), "root_zero")) return rc;
   if (int32_t rc = launched(launch_copy_init(S.D, int(P.n_cuts), S.stream), "copy_init")) return rc;
-  // bound partials: tiles without a root level never write theirs, which stay zero
-  const int nlb = int(2 * (P.n_lbpart + P.n_cut_parts + 1));
-  if (int32_t rc = launched(launch_fill(reinterpret_cast<float *>(S.D.lbpart), 0.0f, nlb, S.stream), "fill")) return rc;
   if (int32_t rc = launched(launch_set_counter(S.D, S.n_hist, S.stream), "set_counter")) return rc;
   // the dataflow launches' error words (generations and tickets stay as they are)
   for (int p = 0; p < 2; ++p)
@@ -523,6 +589,7 @@ int32_t solver_iterate(Solver &S, int32_t n) {
   if (n < 0) return set_error(BDDMP_INVALID_ARG, "negative iteration count");
   if (S.use_graph && n > 0) {
     const Plan &P = *S.plan;
+    if (cell_kind(S)) return cell_iterations(S, n);
     const bool wrap = use_wrap(S);
     if (!S.gexec || (wrap && !S.gexec_wrap) || S.graph_gsel != S.D.gsel)
       if (int32_t rc = capture_iteration(S)) return rc;

@@ -102,8 +102,8 @@ __global__ __launch_bounds__(256) void copy_fwd_wide_kernel(const Dev D, int nn,
 // + gamma delta_fwd (this iteration's forward update). Then the root level's forward messages (the
 // minimum of mu over each node's in-arcs) and the sub-BDD's E (the minimum over its nodes of
 // m_fwd + m_bwd, which is the minimum over the arcs of mu + m_bwd(v)) for the bound, one
-// fixed-shape sum per workgroup into lbpart. update = 0 skips the dual update.
-__global__ __launch_bounds__(256) void copy_bwd_narrow_kernel(const Dev D, int nn, int update, int part0) {
+// fixed-shape sum per workgroup into cut_part. update = 0 skips the dual update.
+__global__ __launch_bounds__(256) void copy_bwd_narrow_kernel(const Dev D, int nn, int update) {
 #pragma clang fp contract(off)
   __shared__ double sh[4];
   const int c = int(blockIdx.x) * 256 + int(threadIdx.x);
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) void copy_bwd_narrow_kernel(const Dev D, int n
     e = double(en);
   }
   const double t = block_sum(e, sh);
-  if (threadIdx.x == 0) D.lbpart[part0 + int(blockIdx.x)] = t;
+  if (threadIdx.x == 0) D.cut_part[int(blockIdx.x)] = t;
 }
 
 __global__ __launch_bounds__(256) void copy_bwd_wide_kernel(const Dev D, int nn, int nc, int update, int part0) {
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256) void copy_bwd_wide_kernel(const Dev D, int nn,
   for (int o = 32; o > 0; o >>= 1) en = fminf(en, __shfl_xor(en, o, 64));
   if (on && lane == 0) D.cut_e[c] = en;
   const double t = block_sum((on && lane == 0) ? double(en) : 0.0, sh);
-  if (threadIdx.x == 0) D.lbpart[part0 + int(blockIdx.x)] = t;
+  if (threadIdx.x == 0) D.cut_part[part0 + int(blockIdx.x)] = t;
 }
 
 // copy state per live pair in canonical order (cuts by row and level, then arc index)
@@ -255,13 +255,13 @@ hipError_t launch_copy_fwd(const Dev &D, int n_cuts, int n_narrow, hipStream_t s
   return hipGetLastError();
 }
 
-// bound partials: one per narrow workgroup from part0, then one per wide workgroup
-hipError_t launch_copy_bwd(const Dev &D, int n_cuts, int n_narrow, int update, int part0, hipStream_t s) {
-  if (n_narrow > 0) copy_bwd_narrow_kernel<<<blocks_of(n_narrow), 256, 0, s>>>(D, n_narrow, update, part0);
+// bound partials: one per narrow workgroup, then one per wide workgroup
+hipError_t launch_copy_bwd(const Dev &D, int n_cuts, int n_narrow, int update, hipStream_t s) {
+  if (n_narrow > 0) copy_bwd_narrow_kernel<<<blocks_of(n_narrow), 256, 0, s>>>(D, n_narrow, update);
   const int nw = n_cuts - n_narrow;
   if (nw > 0)
     copy_bwd_wide_kernel<<<(nw + kCutsPerBlock - 1) / kCutsPerBlock, 256, 0, s>>>(D, n_narrow, n_cuts, update,
-                                                                                   part0 + blocks_of(n_narrow));
+                                                                                   blocks_of(n_narrow));
   return hipGetLastError();
 }
 
