@@ -31,6 +31,8 @@ namespace bddmp {
 
 namespace {
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // float of lane l of the wavefront
 __device__ __forceinline__ float lane_read(float v, int l) {
   return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * l, __float_as_int(v)));
@@ -411,45 +413,45 @@ __global__ __launch_bounds__(BLOCK) void cell_kernel(const Dev D, const CellArgs
   {
     // quads of layers; lanes past the end repeat the last quad (the same values to the same place)
     constexpr int Q = 4;
-    const uint4 *g0 = reinterpret_cast<const uint4 *>(A.w0 + r0.z), *g1 = reinterpret_cast<const uint4 *>(A.w1 + r0.z);
     const int nq = nl / 4;
     for (int q0 = tid; q0 < nq; q0 += Q * BLOCK) {
+      int q[Q];
       float4 l[Q];
-      uint4 a[Q], c[Q];
+#pragma unroll
+      for (int t = 0; t < Q; ++t) q[t] = min(q0 + t * BLOCK, nq - 1);
       if (first) {
 #pragma unroll
         for (int t = 0; t < Q; ++t) {
-          const int4 L = reinterpret_cast<const int4 *>(layer)[min(q0 + t * BLOCK, nq - 1)];
+          const int4 L = reinterpret_cast<const int4 *>(layer)[q[t]];
           // a pad's value is never used
           l[t] = make_float4(D.lam[max(L.x, 0)], D.lam[max(L.y, 0)], D.lam[max(L.z, 0)], D.lam[max(L.w, 0)]);
         }
       } else {
 #pragma unroll
-        for (int t = 0; t < Q; ++t) l[t] = reinterpret_cast<const float4 *>(lamc)[min(q0 + t * BLOCK, nq - 1)];
+        for (int t = 0; t < Q; ++t) l[t] = reinterpret_cast<const float4 *>(lamc)[q[t]];
       }
+      if constexpr (kPair) {
+        // two layers per word
+        uint2 a[Q];
 #pragma unroll
-      for (int t = 0; t < Q; ++t) {
-        const int q = min(q0 + t * BLOCK, nq - 1);
-        if (kPair) {
-          // two layers per word
-          const uint2 h = reinterpret_cast<const uint2 *>(A.w0 + r0.z / 2)[q];
-          a[t] = make_uint4(h.x, h.y, 0u, 0u);
-        } else {
-          a[t] = g0[q];
-          c[t] = g1[q];
+        for (int t = 0; t < Q; ++t) a[t] = reinterpret_cast<const uint2 *>(A.w0 + r0.z / 2)[q[t]];
+#pragma unroll
+        for (int t = 0; t < Q; ++t) reinterpret_cast<uint2 *>(C.w0)[q[t]] = a[t];
+      } else {
+        u32x4 a[Q], c[Q];
+#pragma unroll
+        for (int t = 0; t < Q; ++t) {
+          a[t] = reinterpret_cast<const u32x4 *>(A.w0 + r0.z)[q[t]];
+          c[t] = reinterpret_cast<const u32x4 *>(A.w1 + r0.z)[q[t]];
+        }
+#pragma unroll
+        for (int t = 0; t < Q; ++t) {
+          reinterpret_cast<u32x4 *>(C.w0)[q[t]] = a[t];
+          reinterpret_cast<u32x4 *>(C.w1)[q[t]] = c[t];
         }
       }
 #pragma unroll
-      for (int t = 0; t < Q; ++t) {
-        const int q = min(q0 + t * BLOCK, nq - 1);
-        if (kPair) {
-          reinterpret_cast<uint2 *>(C.w0)[q] = make_uint2(a[t].x, a[t].y);
-        } else {
-          reinterpret_cast<uint4 *>(C.w0)[q] = a[t];
-          reinterpret_cast<uint4 *>(C.w1)[q] = c[t];
-        }
-        reinterpret_cast<float4 *>(C.lam)[q] = l[t];
-      }
+      for (int t = 0; t < Q; ++t) reinterpret_cast<float4 *>(C.lam)[q[t]] = l[t];
     }
   }
   if constexpr (KIND == kCellGen) {
