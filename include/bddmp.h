@@ -70,7 +70,8 @@ typedef struct {
   int32_t hist_cap;       /* bound history ring length on the device (default 4096)           */
   int64_t node_budget;    /* max total BDD nodes, 0 = unlimited                                */
   int32_t tile_work;      /* a tile closes once its general levels hold this many own plus next-
-                             level nodes (0: 2048; the node-parallel path stages up to 2048 of each) */
+                             level nodes (0: 512 to 2048 by the wave's size; the node-parallel path
+                             stages up to 2048 of each)                                            */
   const char *tiling;     /* general-layer path by width class, "g0,g1,g2,g3" (NULL: default
                              "0,0,0,0"); see bddmp_solver_set_groups                             */
   int32_t n_intervals;    /* Sec. 6 split: variable intervals per instance (0 or 1: no split)   */

@@ -41,8 +41,9 @@ constexpr uint32_t kMetaField = 0x3FFu;
 constexpr uint32_t kTileClsShift = 29, kTilePosMask = (1u << 29) - 1u;
 constexpr int kWidthClasses = 4;
 // A tile closes early once its general layers hold this many nodes (own plus child level), so
-// that tiles with wide levels carry comparable work (default; options.tile_work overrides).
-constexpr int64_t kTileWideWork = 2048;
+// that tiles with wide levels carry comparable work: kTileWideWork where a wave fills the GPU, down to
+// kTileFewWork where it does not (defaults; options.tile_work sets one value).
+constexpr int64_t kTileWideWork = 2048, kTileFewWork = 512;
 // nodes of a tile's general own levels, and of their child levels, that the node-parallel (flat)
 // path stages at most (kFlatCap / kTile per lane)
 constexpr int kFlatCap = 2048;

@@ -1100,8 +1100,20 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
         wr.narrow_only = wr.narrow_only && ((P.meta[Lq] >> kMetaWidthShift) & 3u) != 0u;
       }
   };
+  // Nodes per tile of general levels. Where a wave's general levels fill the GPU with tiles of
+  // kTileWideWork nodes (two for each of its 256 compute units), larger tiles amortise a tile's fixed
+  // work; where they do not, a wave takes one tile's latency, which grows with its nodes, so the wave is
+  // split further, down to kTileFewWork. Measured, us per iteration with 2048 / 1024 / 512 / 256 nodes,
+  // one launch per wave: tomography P = 64 3111 / 2716 / 2493 / 2462, P = 80 4017 / 3479 / 3258 / 3236, 16
+  // instances 2979 / 2588 / 2382 / 2340; 256 instances with wave groups 8730 / 9710 (1536) / 12250 / -.
+  auto budget = [&](const std::vector<int32_t> &vars) {
+    if (opt.tile_work > 0) return P.tile_work;
+    int64_t work = 0;
+    for (int32_t i : vars) work += wwork[size_t(i)];
+    return std::min<int64_t>(kTileWideWork, std::max<int64_t>(kTileFewWork, work / 512));
+  };
   for (int32_t t = 1; t <= P.Df; ++t) {
-    tile_pass(fw[t], P.var_nj, wwork, P.var_group, P.tile_work, pos, P.fwd_tiles, P.fwd_big, P.fwd_waves[t - 1]);
+    tile_pass(fw[t], P.var_nj, wwork, P.var_group, budget(fw[t]), pos, P.fwd_tiles, P.fwd_big, P.fwd_waves[t - 1]);
     P.fwd_waves[t - 1].list = 0;
     wave_work(fw[t], P.fwd_waves[t - 1]);
     for (int32_t i : fw[t]) pos += P.var_nj[i];
@@ -1120,7 +1132,7 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
         if (P.bwd_list[pos] != P.bwd_list[w0] + (pos - w0)) contig = false;
       }
     WaveRange &wr = P.bwd_waves[t - 1];
-    tile_pass(bw[t], P.var_nj, wwork, P.var_group, P.tile_work, contig ? P.bwd_list[w0] : w0, P.bwd_tiles, P.bwd_big,
+    tile_pass(bw[t], P.var_nj, wwork, P.var_group, budget(bw[t]), contig ? P.bwd_list[w0] : w0, P.bwd_tiles, P.bwd_big,
               wr);
     wr.list = contig ? 0 : 1;
     wave_work(bw[t], wr);
