@@ -379,7 +379,7 @@ int32_t bddmp_plan_digest(const bddmp_plan *h, uint64_t *digest) {
   digest_add(d, P.inst_lb_const);
   for (const bddmp::CellStage &c : P.cell) {
     digest_add(d, c.rec); digest_add(d, c.work); digest_add(d, c.w0); digest_add(d, c.w1); digest_add(d, c.row);
-    digest_add(d, c.grec); digest_add(d, c.garc); digest_add(d, c.layer); digest_add(d, c.link); digest_add(d, c.term);
+    digest_add(d, c.ga); digest_add(d, c.gb); digest_add(d, c.layer); digest_add(d, c.link); digest_add(d, c.term);
   }
   *digest = d;
   return BDDMP_OK;

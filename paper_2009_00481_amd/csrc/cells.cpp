@@ -29,11 +29,10 @@ namespace bddmp {
 
 namespace {
 
-// bytes of LDS one layer takes: multiplier, link, descriptors, its share of a row part; levels of
-// more than two nodes add their messages and records
-int32_t layer_weight(int32_t w, int32_t wc) {
-  return 22 + (wc > 2 ? 4 * wc + 4 : 0) + (w > 2 || wc > 2 ? 16 + 4 * w : 0);
-}
+// bytes of LDS one layer takes: multiplier, link, its share of a row part; descriptors too unless the
+// plan has levels of more than two nodes (those stages keep them in global memory, and 18 bytes for the
+// 15 a layer takes keep the largest cell under kCellMaxLayers)
+int32_t layer_weight(int32_t wc, bool wide_plan) { return wide_plan ? 18 + (wc > 2 ? 8 : 0) : 22; }
 
 struct UnionFind {
   std::vector<int32_t> up, size;
@@ -97,9 +96,12 @@ void on_threads(int64_t n, int64_t min_chunk, F &&f) {
 
 }  // namespace
 
-// Chooses the stages: per instance the cut of its processing order that makes the larger of A's and
-// B's largest component smallest (no cut, everything in B, when the whole instance fits one
-// workgroup). Leaves P.cell_kind 0 when no cut brings the components within a workgroup's LDS.
+// Chooses the stages: per instance the cut of its processing order that makes A's and B's largest
+// components together smallest (no cut, everything in B, when the whole instance fits one workgroup).
+// The stages run one after the other and a large component's steps in sequence, so the sum follows the
+// time: tracking chains are cut above their links and not in their middle, 32 of them with 200 to 1967
+// detections 141 us per iteration instead of 177. Leaves P.cell_kind 0 when no cut brings the components
+// within a workgroup's LDS.
 void choose_cells(const Problem &p, Plan &P, const std::vector<int64_t> &iptr, const std::vector<int32_t> &ilist,
                   const std::vector<int32_t> &inc_row) {
   P.cell_kind = 0;
@@ -111,8 +113,7 @@ void choose_cells(const Problem &p, Plan &P, const std::vector<int64_t> &iptr, c
       const int32_t c = ilist[size_t(q)], j = inc_row[size_t(c)];
       const Shape &sh = P.shapes[size_t(P.row_shape[size_t(j)])];
       const int32_t l = int32_t(c - P.canon_off[size_t(j)]);
-      wt[size_t(i)] += layer_weight(sh.first[size_t(l) + 1] - sh.first[size_t(l)],
-                                    l + 1 < sh.k ? sh.first[size_t(l) + 2] - sh.first[size_t(l) + 1] : 0);
+      wt[size_t(i)] += layer_weight(l + 1 < sh.k ? sh.first[size_t(l) + 2] - sh.first[size_t(l) + 1] : 0, P.max_width > 2);
     }
   // each instance's variables in processing order
   std::vector<int64_t> iv = p.inst_var.empty() ? std::vector<int64_t>{0, n} : p.inst_var;
@@ -163,7 +164,7 @@ void choose_cells(const Problem &p, Plan &P, const std::vector<int64_t> &iptr, c
       if (uf.largest > kCellLdsMax || uf.largest > cost.first) break;
       if (r > rmax) continue;
       const int32_t a = largest[size_t(r)], b = uf.largest;
-      const std::pair<int32_t, int32_t> c{std::max(a, b), a + b};
+      const std::pair<int32_t, int32_t> c{a + b, std::max(a, b)};
       if (c < cost) {
         cost = c;
         best = r;
@@ -220,24 +221,30 @@ void choose_cells(const Problem &p, Plan &P, const std::vector<int64_t> &iptr, c
 
 namespace {
 
-// Lanes of a stage's workgroups and the layers a cell is filled up to. big, total: layers of the
-// largest component and of the stage; steps: its longest chain.
+// Lanes of a stage's workgroups and the layers a cell is filled up to. total: layers of the stage;
+// largest: the layers of each step of its largest component (big in all).
 //
 // Small components go to one-wavefront cells, whose steps need no barrier. Cells of two-row variables
 // (one lane each) hold up to 1024 layers, others (one lane per layer) up to 256: a step then fills about
 // one wavefront on the grid workloads, and ten or more cells fit a compute unit's LDS. Measured on Potts
 // 256x256x8, us per iteration: 168 with 1024 / 256, 173 with 1024 / 512, 179 with 512 / 512, 198 with 2048
 // layers on two wavefronts. Plans of few cells share the layers out so that every compute unit gets two.
-// A larger component is a cell by itself, with as many lanes as its steps have layers on average.
-void cell_shape(int32_t big, int64_t total, int32_t steps, bool pairs, int32_t &block, int32_t &room) {
+// A larger component is a cell by itself, on the fewest lanes that take at most a quarter more chunks
+// than 512 lanes would.
+void cell_shape(int32_t big, int64_t total, const std::vector<int32_t> &largest, bool pairs, int32_t &block, int32_t &room) {
   const int32_t most = pairs ? 1024 : 256;
   if (big <= most) {
     block = 64;
     room = int32_t(std::min<int64_t>(most, std::max<int64_t>(total / 512, 64)));
     return;
   }
+  auto chunks = [&](int32_t b) {
+    int64_t n = 0;
+    for (int32_t c : largest) n += (c + b - 1) / b;
+    return n;
+  };
   block = 64;
-  while (block < 512 && int64_t(block) * steps < big) block *= 2;
+  while (block < 512 && 4 * chunks(block) > 5 * chunks(512)) block *= 2;
   room = big;
 }
 
@@ -277,19 +284,22 @@ uint32_t cell_arcs(uint32_t arcs, bool last, bool root, bool &x0, bool &y0) {
 
 // one cell's program, before the arrays of equal cells are shared
 struct CellProg {
-  std::vector<uint32_t> h, w1, row, grec, garc, step;  // step: first layer of each step, then the end
-  std::vector<uint32_t> kid;                           // child layer of each layer, 0xFFFF: none in the cell
-  int32_t nl = 0, ns = 0, xa = 0;                      // layers, steps, areas
-  bool pairs = true;                                   // every variable in two rows, every level regular
+  // per layer: area of the parent's link | kCellCount, w1, child and parent layer (0xFFFF: not in the
+  // cell); step: first layer of each step, then the end; plans with wide levels: own area and arcs
+  std::vector<uint32_t> h, w1, kid, dad, row, step, own, arc;
+  int32_t nl = 0, ns = 0, xa = 0;  // layers, steps, areas
+  bool pairs = true;               // every variable in two rows, every level regular
+  bool wide = false;               // some level or child level has more than two nodes
   void clear() {
-    for (auto *v : {&h, &w1, &row, &grec, &garc, &step, &kid}) v->clear();
+    for (auto *v : {&h, &w1, &kid, &dad, &row, &step, &own, &arc}) v->clear();
     nl = ns = xa = 0;
     pairs = true;
+    wide = false;
   }
   uint64_t hash() const {
     uint64_t x = 1469598103934665603ull;
     auto mix = [&](uint64_t v) { x = (x ^ v) * 1099511628211ull; x ^= x >> 29; };
-    for (const auto *a : {&h, &w1, &row, &grec, &garc, &step, &kid}) {
+    for (const auto *a : {&h, &w1, &kid, &dad, &row, &step, &own, &arc}) {
       for (uint32_t v : *a) mix(v);
       mix(a->size());
     }
@@ -297,8 +307,8 @@ struct CellProg {
     return x;
   }
   bool same(const CellProg &o) const {
-    return nl == o.nl && ns == o.ns && xa == o.xa && h == o.h && w1 == o.w1 && row == o.row && grec == o.grec &&
-           garc == o.garc && step == o.step && kid == o.kid;
+    return nl == o.nl && ns == o.ns && xa == o.xa && h == o.h && w1 == o.w1 && kid == o.kid && dad == o.dad && row == o.row &&
+           step == o.step && own == o.own && arc == o.arc;
   }
 };
 
@@ -331,12 +341,18 @@ struct CellBuilder {
       j += nj;
       if (j >= kCellMaxLayers) return false;
     }
+    const bool wide_plan = P.max_width > 2;
     C.nl = (j + 3) & ~3;
     C.ns = int32_t(C.step.size());
     C.step.push_back(uint32_t(j));
     C.h.assign(size_t(C.nl), 0u);
     C.w1.assign(size_t(C.nl), 0u);
     C.kid.assign(size_t(C.nl), 0xFFFFu);
+    if (wide_plan) {
+      C.dad.assign(size_t(C.nl), 0xFFFFu);
+      C.own.assign(size_t(C.nl), 0u);
+      C.arc.assign(4 * size_t(C.nl), 0u);
+    }
     if (layer) layer->assign(size_t(C.nl), -1);
     auto each = [&](auto &&f) {
       for (size_t k = 0; k < nv; ++k)
@@ -362,35 +378,37 @@ struct CellBuilder {
         link[size_t(jj)] = C.xa;
         C.xa += (childw[size_t(L)] + 1) / 2;
       }
+      C.wide = C.wide || ownw[size_t(L)] > 2 || childw[size_t(L)] > 2;
     });
     C.xa = (C.xa + 1) & ~1;
+    if (wide_plan) C.xa += 2;  // the constants
     if (C.xa > 0x7FFF) return false;
-    bool fits = true;
     each([&](int32_t i, int32_t q, int32_t L, int32_t jj) {
       const uint32_t meta = P.meta[size_t(L)];
       const int32_t ch = P.child[size_t(L)], pa = P.parent[size_t(L)], k = part[size_t(jj)], nj = P.var_nj[size_t(i)];
       const bool inner_c = same_stage(ch, st), inner_p = same_stage(pa, st), last = ch < 0, root = pa <= -2;
-      const bool general = ((meta >> kMetaWidthShift) & 3u) == 0u;
+      const int32_t w = ownw[size_t(L)], wc = childw[size_t(L)];
       uint32_t h = uint32_t(inner_p ? link[loc[size_t(pa)]] : C.nl + k * bwp);
-      uint32_t w1 = uint32_t(nj) | uint32_t(q) << kCellPosShift;
+      uint32_t w1 = uint32_t(nj) | uint32_t(q) << kCellPosShift | (last ? kCellLast : 0u);
       if (inner_c) C.kid[size_t(jj)] = uint32_t(loc[size_t(ch)]);
       bool x0 = false, y0 = false;
-      if (last) w1 |= kCellLast;
-      if (general) {
-        const int32_t w = ownw[size_t(L)], wc = childw[size_t(L)];
-        fits = fits && C.grec.size() / 4 < 0xFFFFu && C.garc.size() + size_t(w) < 0xFFFFu;
-        w1 |= kCellGeneral | uint32_t(C.grec.size() / 4) << 16;
-        C.grec.push_back(uint32_t(C.garc.size()) | C.kid[size_t(jj)] << 16);
-        C.grec.push_back(uint32_t(w) | uint32_t(wc) << 4 | (inner_p ? uint32_t(loc[size_t(pa)]) : 0xFFFFu) << 16);
-        C.grec.push_back(uint32_t(link[size_t(jj)]));
-        C.grec.push_back(0u);
-        for (int32_t u = 0; u < w; ++u) C.garc.push_back(P.garcs[size_t(P.own_slot[size_t(L)] + u)]);
+      if (w > 2 || wc > 2) {
         C.pairs = false;
       } else {
         const uint32_t arcs = cell_arcs(meta & 0xFFu, last, root, x0, y0);
         w1 |= arcs << 16;
         if (arcs == kArcsCount) h |= kCellCount;
         C.pairs = C.pairs && nj == 2 && (arcs == kArcsCount || arcs == kArcsTake);
+      }
+      if (wide_plan) {
+        if (inner_p) C.dad[size_t(jj)] = uint32_t(loc[size_t(pa)]);
+        C.own[size_t(jj)] = uint32_t(link[size_t(jj)]) | uint32_t(w) << 16 | uint32_t(wc) << 20;
+        const uint32_t consts = 2u * uint32_t(C.xa - 2), f0 = 2u * uint32_t(link[size_t(jj)]);
+        auto at_float = [&](uint32_t c) { return c < kTop ? f0 + c : consts + (c == kTop ? 0u : 1u); };
+        for (int32_t u = 0; u < 4; ++u) {
+          const uint32_t a = u < w ? P.garcs[size_t(P.own_slot[size_t(L)] + u)] : kBot | kBot << 16;
+          C.arc[4 * size_t(jj) + size_t(u)] = at_float(a & 0xFFFFu) | at_float(a >> 16) << 16;
+        }
       }
       uint32_t &r = C.row[size_t(k)];
       if (root) r |= kCellRowRoot;
@@ -399,28 +417,30 @@ struct CellBuilder {
       C.w1[size_t(jj)] = w1;
       if (layer) (*layer)[size_t(jj)] = L;
     });
-    return fits;
+    return true;
   }
 };
 
 // The class bits of layers [j0, j1).
-uint32_t chunk_class(const CellProg &C, int32_t j0, int32_t j1) {
-  uint32_t cls = kCellRegular | kCellTakes | kCellCounts, longest = 1;
+uint32_t chunk_class(const CellProg &C, int32_t kind, int32_t j0, int32_t j1) {
+  uint32_t cls = kCellRegular | kCellTakes | kCellCounts, longest = 1, nodes = 1;
   for (int32_t j = j0; j < j1; ++j) {
     const uint32_t y = C.w1[size_t(j)];
     if (!(y & 0x7Fu)) continue;
     longest = std::max(longest, y & 0x7Fu);
-    const uint32_t a = (y & kCellGeneral) ? 0xFFu : y >> 16;
+    if (kind == kCellGen) nodes = std::max(nodes, (C.own[size_t(j)] >> 16) & 0xFu);
+    const uint32_t a = y >> 16;
     if (a != kArcsCount) cls &= ~kCellCounts;
     if (a != kArcsTake) cls &= ~kCellTakes;
     if (a != kArcsCount && a != kArcsTake) cls &= ~kCellRegular;
   }
+  if (kind == kCellGen) cls = (nodes - 1u) << 24;
   return cls | std::min(longest - 1, 15u) << 28;
 }
 
 // LDS of a cell: the kernel's arrays, and slack for the reads of lanes past a chunk's end
-int32_t cell_lds(int32_t nl, int32_t nrow, int32_t xa, int32_t ngen, int32_t narc, int32_t kind, int32_t block) {
-  return 8 * xa + 16 * ngen + 4 * nl + (kind == kCellPair ? 2 : 8) * nl + 4 * nrow + 4 * narc + 16 * block;
+int32_t cell_lds(int32_t nl, int32_t nrow, int32_t xa, int32_t kind, int32_t block) {
+  return 8 * xa + 4 * nl + (kind == kCellPair ? 2 : (kind == kCellLayers ? 8 : 0)) * nl + 4 * nrow + 16 * block;
 }
 
 }  // namespace
@@ -483,7 +503,14 @@ bool build_cells(Plan &P, const std::vector<int64_t> &iptr, const std::vector<in
     for (int32_t c : corder)
       if (cstage[size_t(c)] == st) total += clayers[size_t(c)];
     int32_t room = 0;
-    cell_shape(big, total, steps[st], pairs[st] && st == 1, S.block, room);
+    std::vector<int32_t> hist(size_t(steps[st]), 0);
+    int32_t bigc = -1;
+    for (int32_t c : corder)
+      if (cstage[size_t(c)] == st && clayers[size_t(c)] == big) bigc = c;
+    if (big > 256)
+      for (int32_t i = 0; i < n; ++i)
+        if (P.var_comp[size_t(i)] == bigc) hist[size_t(vstep[size_t(i)])] += P.var_nj[size_t(i)];
+    cell_shape(big, total, hist, pairs[st] && st == 1, S.block, room);
     room = std::max(room, big);
     int32_t nc = 0, fill = 0, g = -1;
     for (int32_t c : corder) {
@@ -577,44 +604,54 @@ bool build_cells(Plan &P, const std::vector<int64_t> &iptr, const std::vector<in
     });
     for (int32_t k = 0; k < nc; ++k)
       if (differs[size_t(k)]) append(k);
+    auto lds = [&](int32_t kind) {
+      int32_t most = 0;
+      for (const CellProg &C : prog) most = std::max(most, cell_lds(C.nl, int32_t(C.row.size()), C.xa, kind, S.block));
+      return most;
+    };
     S.kind = all_pairs && st == 1 ? kCellPair : kCellLayers;
     for (const CellProg &C : prog)
-      if (!C.grec.empty()) S.kind = kCellGen;
+      if (C.wide) S.kind = kCellGen;
+    if (S.kind == kCellLayers && P.max_width > 2 && lds(S.kind) > kCellLdsCap) S.kind = kCellGen;
+    S.lds = lds(S.kind);
     // concatenated programs: two-row stages pack their descriptors by variable
-    std::vector<int32_t> wbase, kbase, nwork, tbase, gbase, abase;
+    std::vector<int32_t> wbase, kbase, nwork, tbase;
+    int64_t total_w = 0;
     for (const CellProg &C : prog) {
-      wbase.push_back(int32_t(S.w1.size()));
+      wbase.push_back(int32_t(total_w));
       kbase.push_back(int32_t(S.work.size()));
       tbase.push_back(int32_t(S.row.size()));
-      gbase.push_back(int32_t(S.grec.size() / 4));
-      abase.push_back(int32_t(S.garc.size()));
-      if (S.w1.size() + C.w1.size() >= size_t(INT32_MAX) / 2 || S.garc.size() + C.garc.size() >= size_t(INT32_MAX) / 2)
-        return false;
+      total_w += C.nl;
+      if (total_w >= INT32_MAX / 8) return false;
       const int32_t per = S.kind == kCellPair ? 2 : 1;
-      for (int32_t j = 0; j < C.nl; j += per)
-        S.w0.push_back(C.h[size_t(j)] | (per == 2 ? C.h[size_t(j) + 1] : C.kid[size_t(j)]) << 16);
+      if (S.kind == kCellGen) {
+        for (int32_t j = 0; j < C.nl; ++j) {
+          const uint32_t o = C.own[size_t(j)];
+          S.ga.insert(S.ga.end(), {(C.h[size_t(j)] & 0x7FFFu) | (o & 0xFFFFu) << 16, C.kid[size_t(j)] | C.dad[size_t(j)] << 16,
+                                   (C.w1[size_t(j)] & 0xFFFFu) | (o & 0xFF0000u), 0u});
+        }
+        S.gb.insert(S.gb.end(), C.arc.begin(), C.arc.end());
+      } else {
+        for (int32_t j = 0; j < C.nl; j += per)
+          S.w0.push_back(C.h[size_t(j)] | (per == 2 ? C.h[size_t(j) + 1] : C.kid[size_t(j)]) << 16);
+        S.w1.insert(S.w1.end(), C.w1.begin(), C.w1.end());
+      }
       for (int32_t s = 0; s < C.ns; ++s) {
         const int32_t e = int32_t(C.step[size_t(s) + 1]);
         for (int32_t j = int32_t(C.step[size_t(s)]); j < e; j += per * S.block) {
           const int32_t j1 = std::min(e, j + per * S.block);
-          S.work.push_back(uint32_t(j / per) | uint32_t((j1 - j) / per) << 13 | chunk_class(C, j, j1) |
+          S.work.push_back(uint32_t(j / per) | uint32_t((j1 - j) / per) << 13 | chunk_class(C, S.kind, j, j1) |
                            (j == int32_t(C.step[size_t(s)]) ? kCellStepBegin : 0u) | (j1 == e ? kCellStepEnd : 0u));
         }
       }
       nwork.push_back(int32_t(S.work.size()) - kbase.back());
-      S.w1.insert(S.w1.end(), C.w1.begin(), C.w1.end());
       S.row.insert(S.row.end(), C.row.begin(), C.row.end());
-      S.grec.insert(S.grec.end(), C.grec.begin(), C.grec.end());
-      S.garc.insert(S.garc.end(), C.garc.begin(), C.garc.end());
-      S.lds = std::max(S.lds, cell_lds(C.nl, int32_t(C.row.size()), C.xa, int32_t(C.grec.size() / 4), int32_t(C.garc.size()),
-                                       S.kind, S.block));
     }
     for (int32_t k = 0; k < nc; ++k) {
       const size_t t = size_t(tmpl[size_t(k)]);
       const CellProg &C = prog[t];
       S.rec.insert(S.rec.end(), {C.nl, nwork[t], wbase[t], kbase[t], int32_t(lbase[size_t(k)]), int32_t(rbase[size_t(k)]),
-                                 C.xa, 0, int32_t(C.row.size()), tbase[t], int32_t(C.grec.size() / 4), gbase[t],
-                                 int32_t(C.garc.size()), abase[t], 0, 0});
+                                 C.xa, 0, int32_t(C.row.size()), tbase[t], 0, 0});
     }
     if (S.lds > kCellLdsCap) return false;
   }
@@ -637,7 +674,8 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
   std::atomic<const char *> bad{nullptr};
   for (int st = 0; st < 2; ++st) {
     const CellStage &S = P.cell[st];
-    if (S.rec.size() != 16 * size_t(S.n_cells) || S.w0.size() * (S.kind == kCellPair ? 2 : 1) != S.w1.size() || S.link.size() != S.term.size() || S.bw < 2 ||
+    if (S.rec.size() != 12 * size_t(S.n_cells) || S.w0.size() * (S.kind == kCellPair ? 2 : 1) != S.w1.size() ||
+        S.ga.size() != S.gb.size() || S.link.size() != S.term.size() || S.bw < 2 ||
         (S.bw & 1) || S.bw != P.cell[1 - st].bw)
       return "cell arrays";
     on_threads(S.n_cells, 64, [&](int64_t k0, int64_t k1) {
@@ -645,26 +683,27 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
       std::vector<int32_t> step_of, part_f, part_b;
       std::vector<std::pair<int32_t, int32_t>> wide;
       for (int64_t k = k0; k < k1; ++k) {
-        const int32_t *r = &S.rec[16 * size_t(k)];
-        for (int q = 0; q < 14; ++q)
+        const int32_t *r = &S.rec[12 * size_t(k)];
+        for (int q = 0; q < 12; ++q)
           if (r[q] < 0) return fail("cell record");
         const int32_t nl = r[0], nw = r[1], xa = r[6], nrow = r[8], bwp = S.bw / 2, per = S.kind == kCellPair ? 2 : 1;
-        if (nl < 4 || (nl & 3) || nl > 0x1FFF || nw < 1 || (r[2] & 3) || (r[4] & 3) || size_t(r[2]) + size_t(nl) > S.w1.size() ||
+        const bool gen = S.kind == kCellGen;
+        if (nl < 4 || (nl & 3) || nl > 0x1FFF || nw < 1 || (r[2] & 3) || (r[4] & 3) ||
+            size_t(r[2]) + size_t(nl) > (gen ? S.ga.size() / 4 : S.w1.size()) ||
             size_t(r[3]) + size_t(nw) > S.work.size() || size_t(r[4]) + size_t(nl) > S.layer.size() || nrow < 1 ||
             size_t(r[5]) + size_t(nrow) > S.link.size() || size_t(r[9]) + size_t(nrow) > S.row.size() ||
-            4 * (size_t(r[11]) + size_t(r[10])) > S.grec.size() || size_t(r[13]) + size_t(r[12]) > S.garc.size() ||
-            (xa & 1) || xa < nl + nrow * bwp || xa > 0x7FFF ||
-            cell_lds(nl, nrow, xa, r[10], r[12], S.kind, S.block) > S.lds || (S.kind != kCellGen && r[10]))
+            (xa & 1) || xa < nl + nrow * bwp + (gen ? 2 : 0) || xa > 0x7FFF || cell_lds(nl, nrow, xa, S.kind, S.block) > S.lds)
           return fail("cell record");
-        const uint32_t *w1 = &S.w1[size_t(r[2])], *row = S.row.data() + r[9], *work = &S.work[size_t(r[3])];
+        const uint32_t *row = S.row.data() + r[9], *work = &S.work[size_t(r[3])];
         const int32_t *lay = &S.layer[size_t(r[4])];
+        auto word = [&](int32_t j, int q) { return S.ga[4 * size_t(r[2] + j) + size_t(q)]; };
+        auto w1 = [&](int32_t j) { return gen ? word(j, 2) : S.w1[size_t(r[2] + j)]; };
         auto parent_area = [&](int32_t j) {  // with kCellCount in bit 15
+          if (gen) return word(j, 0) & 0xFFFFu;
           if (per == 1) return S.w0[size_t(r[2] + j)] & 0xFFFFu;
           return (S.w0[size_t((r[2] + j) / 2)] >> (16 * (j & 1))) & 0xFFFFu;
         };
-        auto area = [&](int32_t j) {  // layer j's link
-          return (w1[j] & kCellGeneral) ? int32_t(S.grec[4 * (size_t(r[11]) + (w1[j] >> 16)) + 2]) : j;
-        };
+        auto area = [&](int32_t j) { return gen ? int32_t(word(j, 0) >> 16) : j; };  // layer j's link
         // chunks: consecutive from the first layer on, inside their steps
         step_of.assign(size_t(nl), -1);
         std::vector<int32_t> chunk_of(size_t(nl), -1), chunk0(size_t(nw), 0);
@@ -683,12 +722,11 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
           at_j = j0 + c;
         }
         for (int32_t j = 0; j < nl; ++j) {
-          if ((lay[j] >= 0) != ((w1[j] & 0x7Fu) != 0u) || lay[j] >= P.I || (lay[j] >= 0 && step_of[size_t(j)] < 0))
+          if ((lay[j] >= 0) != ((w1(j) & 0x7Fu) != 0u) || lay[j] >= P.I || (lay[j] >= 0 && step_of[size_t(j)] < 0))
             return fail("cell layer");
           if (lay[j] < 0) continue;
           seen[size_t(lay[j])] = 1;
           ++total;
-          if ((w1[j] & kCellGeneral) && (w1[j] >> 16) >= uint32_t(r[10])) return fail("cell general record");
         }
         // row parts: walks along the children cover each layer once; links and terms
         part_f.assign(size_t(nl), -1);
@@ -730,7 +768,7 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
           const int32_t L = lay[j];
           if (L < 0) continue;
           ++layers;
-          const int32_t s = step_of[size_t(j)], len = int32_t(w1[j] & 0x7Fu), pos = int32_t((w1[j] >> kCellPosShift) & 0x7Fu);
+          const int32_t s = step_of[size_t(j)], len = int32_t(w1(j) & 0x7Fu), pos = int32_t((w1(j) >> kCellPosShift) & 0x7Fu);
           const int32_t v = P.layer_var[size_t(L)], h = j - pos;
           // a variable's layers lie in one chunk, on one wavefront
           if (len != P.var_nj[size_t(v)] || pos != L - P.var_first[size_t(v)] || h < 0 || h + len > nl ||
@@ -740,27 +778,35 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
           const int32_t c0 = chunk0[size_t(chunk_of[size_t(j)])];
           if (per == 1 && (h - c0) / 64 != (h + len - 1 - c0) / 64) return fail("cell segment");
           const int32_t ch = P.child[size_t(L)], pa = P.parent[size_t(L)], w = ownw[size_t(L)], wc = childw[size_t(L)];
-          const bool general = ((P.meta[size_t(L)] >> kMetaWidthShift) & 3u) == 0u;
-          if (bool(w1[j] & kCellLast) != (ch < 0) || bool(w1[j] & kCellGeneral) != general) return fail("cell ends");
+          if (bool(w1(j) & kCellLast) != (ch < 0)) return fail("cell ends");
+          if (!gen && (w > 2 || wc > 2)) return fail("cell kind");
           const int32_t jc = ch >= 0 ? local(ch) : -1, jp = pa >= 0 ? local(pa) : -1;
           if ((jc >= 0 && step_of[size_t(jc)] <= s) || (jp >= 0 && step_of[size_t(jp)] >= s)) return fail("cell step order");
           if ((jc < 0) != (part_b[size_t(j)] >= 0) || (jp < 0) != (part_f[size_t(j)] >= 0)) return fail("cell row ends");
           if (int32_t(parent_area(j) & 0x7FFFu) != (jp >= 0 ? area(jp) : nl + part_f[size_t(j)] * bwp)) return fail("cell parent area");
-          if (per == 1 && int32_t(S.w0[size_t(r[2] + j)] >> 16) != (jc >= 0 ? jc : 0xFFFF)) return fail("cell child");
-          if (general) {
-            const uint32_t *g = &S.grec[4 * (size_t(r[11]) + (w1[j] >> 16))];
-            const int32_t a0 = int32_t(g[0] & 0xFFFFu);
-            if (int32_t(g[1] & 0xFu) != w || int32_t((g[1] >> 4) & 0xFu) != wc || a0 + w > r[12] ||
-                int32_t(g[0] >> 16) != (jc >= 0 ? jc : 0xFFFF) || int32_t(g[1] >> 16) != (jp >= 0 ? jp : 0xFFFF))
-              return fail("cell general record");
-            for (int32_t u = 0; u < w; ++u)
-              if (S.garc[size_t(r[13]) + size_t(a0 + u)] != P.garcs[size_t(P.own_slot[size_t(L)] + u)]) return fail("cell general arcs");
-            const int32_t o = area(j);
-            if ((wc <= 2) != (o == j) || o + (wc + 1) / 2 > xa) return fail("cell general areas");
+          const int32_t kid = jc >= 0 ? jc : 0xFFFF;
+          if (gen) {
+            const int32_t o = area(j), consts = 2 * (xa - 2);
+            if (int32_t(word(j, 1) & 0xFFFFu) != kid || int32_t(word(j, 1) >> 16) != (jp >= 0 ? jp : 0xFFFF)) return fail("cell neighbours");
+            if (w > 4 || wc > 4 || int32_t((word(j, 2) >> 16) & 0xFu) != w || int32_t((word(j, 2) >> 20) & 0xFu) != wc)
+              return fail("cell widths");
+            if ((wc <= 2) != (o == j) || o + (wc + 1) / 2 > xa - 2) return fail("cell areas");
             if (wc > 2) wide.emplace_back(o, (wc + 1) / 2);
-          } else {
+            for (int32_t u = 0; u < 4; ++u) {
+              const uint32_t a = u < w ? P.garcs[size_t(P.own_slot[size_t(L)] + u)] : kBot | kBot << 16;
+              for (int hi = 0; hi < 2; ++hi) {
+                const uint32_t c = hi ? a >> 16 : a & 0xFFFFu, x = S.gb[4 * size_t(r[2] + j) + size_t(u)];
+                if (int32_t(hi ? x >> 16 : x & 0xFFFFu) != (c < kTop ? 2 * o + int32_t(c) : consts + (c == kTop ? 0 : 1)))
+                  return fail("cell arcs");
+              }
+            }
+            if (w - 1 > int32_t((work[chunk_of[size_t(j)]] >> 24) & 3u)) return fail("cell chunk class");
+          } else if (per == 1 && int32_t(S.w0[size_t(r[2] + j)] >> 16) != kid) {
+            return fail("cell child");
+          }
+          if (!gen) {
             // the arcs decode to the layer's, terminals through the virtual child level
-            const uint32_t arcs = w1[j] >> 16;
+            const uint32_t arcs = w1(j) >> 16;
             if (bool(parent_area(j) & kCellCount) != (arcs == kArcsCount)) return fail("cell arcs");
             for (int q = 0; q < (pa <= -2 ? 2 : 4); ++q) {
               const uint32_t c = (arcs >> (2 * q)) & 3u, o = (P.meta[size_t(L)] >> (2 * q)) & 3u;
@@ -775,10 +821,13 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
             if (S.kind == kCellPair && (len != 2 || (h & 1) || (arcs != kArcsCount && arcs != kArcsTake))) return fail("cell pair");
           }
           const uint32_t cls = work[chunk_of[size_t(j)]];
-          const uint32_t a = general ? 0xFFu : w1[j] >> 16;
-          if (((cls & kCellRegular) && a != kArcsCount && a != kArcsTake) || ((cls & kCellTakes) && a != kArcsTake) ||
-              ((cls & kCellCounts) && a != kArcsCount) || (cls >> 28) < std::min(uint32_t(len) - 1u, 15u))
-            return fail("cell chunk class");
+          if ((cls >> 28) < std::min(uint32_t(len) - 1u, 15u)) return fail("cell chunk class");
+          if (!gen) {
+            const uint32_t a = w1(j) >> 16;
+            if (((cls & kCellRegular) && a != kArcsCount && a != kArcsTake) || ((cls & kCellTakes) && a != kArcsTake) ||
+                ((cls & kCellCounts) && a != kArcsCount))
+              return fail("cell chunk class");
+          }
         }
         if (walked != layers) return fail("cell row part");
         std::sort(wide.begin(), wide.end());

@@ -17,8 +17,8 @@
 // touches is in LDS or read ahead (a global round trip per step took twice the time). Between calls of
 // iterate the multipliers are in storage order; inside a run they are kept in cell order, where a
 // cell's are contiguous. Measured, us per iteration against one launch per wave replayed as a graph:
-// Potts 256x256x8 168 (367), 128x128x4 29 (61), 16x16x4 15 (49); Potts 8x8x3, whole in one workgroup, 11
-// (38).
+// Potts 256x256x8 168 (367), 128x128x4 29 (61), 16x16x4 15 (49); Potts 8x8x3, whole in one workgroup, 10
+// (38); a batch of 32 tracking instances of 200 to 1967 detections 141 (1040).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -51,6 +51,11 @@ __device__ __forceinline__ float lane_before(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xF, 0xF, false));
 }
 
+// the following one (wave_shl:1)
+__device__ __forceinline__ float lane_after(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, false));
+}
+
 // s / n for a row count n, with r = 1 / n rounded: one correction of s * r by the exact remainder is the
 // correctly rounded quotient (checked for every mantissa and n <= 64) while nothing underflows or
 // overflows; the division itself elsewhere.
@@ -71,17 +76,13 @@ __device__ __forceinline__ float over_count(float s, float n, float r) {
 struct Cell {
   float2 *X;
   float *lam;
-  uint32_t *w0, *w1;     // descriptors (internal.h)
+  uint32_t *w0, *w1;     // descriptors (internal.h); kCellGen reads ga, gb from global memory instead
+  const u32x4 *ga, *gb;
   const uint32_t *work;  // global: the chunks of the steps (internal.h)
   uint32_t *row;
-  uint4 *grec;
-  uint32_t *garc;
   int nwork, nrow, nl;
+  int consts;            // kCellGen: the float index of the constants behind terminal arcs
 };
-
-__device__ __forceinline__ float cell_c16(const float *b, uint32_t c) {
-  return c < kTop ? b[c] : (c == kTop ? 0.0f : INFINITY);
-}
 
 // Regular levels: 0-arcs keep the node, and either node 0's 1-arc moves to node 1 (c, a counting
 // level) or node 1's to node 0. These closed forms drop only terms that are +inf.
@@ -111,78 +112,60 @@ __device__ __forceinline__ float2 narrow_bstep(uint32_t a, float2 b, float lam) 
                      fminf(c2val((a >> 4) & 3u, b), c2val((a >> 6) & 3u, b) + lam));
 }
 
-// levels of more than two nodes (or above one), node by node: from is the area of the forward messages
-// (the parent's link), own the layer's link
-__device__ __forceinline__ void general_push(const Cell &C, uint4 g, int from, float lam) {
-  const float *fp = reinterpret_cast<const float *>(C.X + from);
-  float *cp = reinterpret_cast<float *>(C.X + g.z);
-  const uint32_t *arc = C.garc + (g.x & 0xFFFFu);
-  const int w = int(g.y & 0xFu), wc = int((g.y >> 4) & 0xFu);
-  for (int q = 0; q < ((wc + 1) & ~1); ++q) cp[q] = INFINITY;
-  for (int u = 0; u < w; ++u) {
-    const uint32_t lo = arc[u] & 0xFFFFu, hi = arc[u] >> 16;
-    const float fu = fp[u];
-    if (lo < kTop) cp[lo] = fminf(cp[lo], fu);
-    if (hi < kTop) cp[hi] = fminf(cp[hi], fu + lam);
+// Levels of up to four nodes (kCellGen). Each arc names the float of X behind it: its child's on the
+// layer's own link, or one of the constants 0 (TOP) and +inf (BOT, and the arcs of absent nodes), so a
+// node costs two LDS reads and no decoding. w: nodes of the level, or of the widest in the chunk.
+struct Arcs {
+  u32x4 a;  // per node lo | hi << 16
+  __device__ __forceinline__ int lo(int u) const { return int(a[u] & 0xFFFFu); }
+  __device__ __forceinline__ int hi(int u) const { return int(a[u] >> 16); }
+};
+template <int W>
+__device__ __forceinline__ void gen_push(const Cell &C, u32x4 d, Arcs arc, const float *f, float lam) {
+  float *x = reinterpret_cast<float *>(C.X);
+  const int own = int(d[0] >> 16);
+  // the link's messages start at +inf (one-node levels keep their second float there); a lane owns the
+  // link, so the order of the minima does not matter
+  C.X[own] = make_float2(INFINITY, INFINITY);
+  if (((d[2] >> 20) & 7u) > 2u) C.X[own + 1] = make_float2(INFINITY, INFINITY);
+#pragma unroll
+  for (int u = 0; u < W; ++u) {
+    if (arc.lo(u) < C.consts) __hip_atomic_fetch_min(x + arc.lo(u), f[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    if (arc.hi(u) < C.consts) __hip_atomic_fetch_min(x + arc.hi(u), f[u] + lam, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
   }
 }
-__device__ __forceinline__ void general_bstep(const Cell &C, uint4 g, int to, float lam) {
-  const float *bp = reinterpret_cast<const float *>(C.X + g.z);
-  float *pp = reinterpret_cast<float *>(C.X + to);
-  const uint32_t *arc = C.garc + (g.x & 0xFFFFu);
-  const int w = int(g.y & 0xFu);
-  for (int u = 0; u < w; ++u) pp[u] = fminf(cell_c16(bp, arc[u] & 0xFFFFu), cell_c16(bp, arc[u] >> 16) + lam);
-  if (w & 1) pp[w] = INFINITY;
+// lo, hi: what the arcs carry
+template <int W>
+__device__ __forceinline__ void gen_bstep(const Cell &C, u32x4 d, const float *lo, const float *hi, float lam) {
+  const int p = int(d[0] & 0x7FFFu);
+  C.X[p] = make_float2(vmin(lo[0], hi[0] + lam), vmin(lo[1], hi[1] + lam));
+  if constexpr (W > 2)
+    if (((d[2] >> 16) & 7u) > 2u) C.X[p + 1] = make_float2(vmin(lo[2], hi[2] + lam), vmin(lo[3], hi[3] + lam));
 }
 
 // Order between a step's LDS writes and the next step's reads. One wavefront's LDS accesses are
 // executed in the order it issues them, so a one-wavefront workgroup only keeps the compiler from
-// moving them; larger ones meet at a barrier.
+// moving them; larger ones meet at a barrier once their LDS accesses are done. (__syncthreads would
+// also wait for the descriptors that a pass has in flight from global memory.)
 template <int BLOCK>
 __device__ __forceinline__ void step_sync() {
   if (BLOCK == 64) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   } else {
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
   }
 }
 
-// One layer's part of a step: min-marginals, J_i exchange, update, and the message it passes on. A
-// variable's layers sit on consecutive lanes of one wavefront, so the exchange is lane moves. f: the
-// messages on the parent's link (area p), b: those on its own; longest: one less than the most rows of
-// a variable of the chunk (-1: 16 or more); rcp: 1 / (lane + 1).
-template <int DIR, bool GEN>
-__device__ __forceinline__ void layer_step(const Cell &C, uint32_t d0, uint32_t d1, float lam, float2 f, float2 b, int j,
-                                           bool regular, int longest, float rcp) {
-  const int p = int(d0 & 0x7FFFu);
-  const int len = int(d1 & 0x7Fu);
-  const bool gen = GEN && (d1 & kCellGeneral) != 0u;
-  const bool s = (d0 & kCellCount) != 0u;
-  const uint32_t arcs = d1 >> 16;
-  uint4 g = make_uint4(0u, 0u, 0u, 0u);
-  float m0 = INFINITY, m1 = INFINITY;
-  if (regular) {
-    m0 = vmin(f.x + b.x, f.y + b.y);
-    m1 = regular_m1(s, f, b, lam);
-  } else if (!gen) {
-    m0 = fminf(f.x + c2val(arcs & 3u, b), f.y + c2val((arcs >> 4) & 3u, b));
-    m1 = fminf((f.x + lam) + c2val((arcs >> 2) & 3u, b), (f.y + lam) + c2val((arcs >> 6) & 3u, b));
-  } else {
-    g = C.grec[arcs];
-    const float *fp = reinterpret_cast<const float *>(C.X + p);
-    const float *bp = reinterpret_cast<const float *>(C.X + g.z);
-    const uint32_t *arc = C.garc + (g.x & 0xFFFFu);
-    const int w = int(g.y & 0xFu);
-    for (int u = 0; u < w; ++u) {
-      m0 = fminf(m0, fp[u] + cell_c16(bp, arc[u] & 0xFFFFu));
-      m1 = fminf(m1, (fp[u] + lam) + cell_c16(bp, arc[u] >> 16));
-    }
-  }
-  const float dd = m1 - m0;
-  // J_i sum in ascending row order; rows forcing the variable (infinite difference) apart. The lanes
-  // of a segment are all here, and the branch is uniform over the wavefront's active lanes.
-  const int at = int((d1 >> kCellPosShift) & 0x7Fu), h = (int(threadIdx.x) & 63) - at;
+// J_i exchange and update: the layer's new multiplier from its difference dd. A variable's layers sit
+// on consecutive lanes of one wavefront (at: the layer's place among its len), so the exchange is lane
+// moves; the sum runs in ascending row order, rows forcing the variable (infinite difference) apart.
+// The lanes of a segment are all here, and the branch is uniform over the wavefront's active lanes.
+// longest: one less than the most rows of a variable of the chunk (-1: 16 or more); rcp: 1 / (lane + 1).
+__device__ __forceinline__ float exchange(float lam, float dd, int len, int at, int longest, float rcp) {
+  const int h = (int(threadIdx.x) & 63) - at;
   if (longest < 0 || __any(isinf(dd))) {
     float sum = 0.0f;
     int nf = 0;
@@ -191,26 +174,60 @@ __device__ __forceinline__ void layer_step(const Cell &C, uint32_t d0, uint32_t 
       if (isinf(dq)) ++nf;
       else sum += dq;
     }
-    lam = updated(lam, dd, nf ? sum / float(nf) : sum / float(len), nf);
-  } else {
-    // running sums handed from lane to lane, the last lane's to all
-    float sum = dd;
-    for (int t = 1; t <= longest; ++t) {
-      const float x = lane_before(sum);
-      if (at == t) sum = x + dd;
-    }
-    const float r = lane_read(rcp, len - 1);
-    lam = (lam - dd) + over_count(lane_read(sum, h + len - 1), float(len), r);
+    return updated(lam, dd, nf ? sum / float(nf) : sum / float(len), nf);
   }
+  if (longest <= 1) {
+    // one or two rows: the neighbour's difference by a register move
+    const float up = lane_after(dd), dn = lane_before(dd);
+    const float sum = at ? dn + dd : dd + up;
+    return (lam - dd) + (len == 1 ? dd : sum * 0.5f);
+  }
+  // running sums handed from lane to lane, the last lane's to all
+  float sum = dd;
+  for (int t = 1; t <= longest; ++t) {
+    const float x = lane_before(sum);
+    if (at == t) sum = x + dd;
+  }
+  const float r = lane_read(rcp, len - 1);
+  return (lam - dd) + over_count(lane_read(sum, h + len - 1), float(len), r);
+}
+
+// One narrow layer's part of a step: min-marginals, exchange, update, and the message it passes on.
+// f: the messages on the parent's link (area p), b: those on its own.
+template <int DIR>
+__device__ __forceinline__ void layer_step(const Cell &C, uint32_t d0, uint32_t d1, float lam, float2 f, float2 b, int j,
+                                           bool regular, int longest, float rcp) {
+  const bool s = (d0 & kCellCount) != 0u;
+  const uint32_t arcs = d1 >> 16;
+  float m0, m1;
+  if (regular) {
+    m0 = vmin(f.x + b.x, f.y + b.y);
+    m1 = regular_m1(s, f, b, lam);
+  } else {
+    m0 = fminf(f.x + c2val(arcs & 3u, b), f.y + c2val((arcs >> 4) & 3u, b));
+    m1 = fminf((f.x + lam) + c2val((arcs >> 2) & 3u, b), (f.y + lam) + c2val((arcs >> 6) & 3u, b));
+  }
+  lam = exchange(lam, m1 - m0, int(d1 & 0x7Fu), int((d1 >> kCellPosShift) & 0x7Fu), longest, rcp);
   C.lam[j] = lam;
-  if (gen) {
-    if (DIR == kFwd) general_push(C, g, p, lam);
-    else general_bstep(C, g, p, lam);
-  } else if (DIR == kFwd) {
-    C.X[j] = regular ? regular_push(s, f, lam) : narrow_push(arcs, f, lam);
-  } else {
-    C.X[p] = regular ? regular_bstep(s, b, lam) : narrow_bstep(arcs, b, lam);
+  if (DIR == kFwd) C.X[j] = regular ? regular_push(s, f, lam) : narrow_push(arcs, f, lam);
+  else C.X[d0 & 0x7FFFu] = regular ? regular_bstep(s, b, lam) : narrow_bstep(arcs, b, lam);
+}
+
+// The same for a layer of any kind in a cell with levels of up to four nodes (W: 2 or 4, the chunk's
+// widest). f: its own forward messages; lo, hi: what its arcs carry. Absent nodes take what happens to
+// lie behind their messages: their arcs are +inf, and a minimum drops the NaN that some bit patterns give.
+template <int DIR, int W>
+__device__ __forceinline__ void gen_step(const Cell &C, u32x4 d, Arcs arc, float lam, const float *f, const float *lo,
+                                         const float *hi, int j, int longest, float rcp) {
+  float m0 = vmin(f[0] + lo[0], f[1] + lo[1]), m1 = vmin((f[0] + lam) + hi[0], (f[1] + lam) + hi[1]);
+  if constexpr (W > 2) {
+    m0 = vmin(vmin(m0, f[2] + lo[2]), f[3] + lo[3]);
+    m1 = vmin(vmin(m1, (f[2] + lam) + hi[2]), (f[3] + lam) + hi[3]);
   }
+  lam = exchange(lam, m1 - m0, int(d[2] & 0x7Fu), int((d[2] >> kCellPosShift) & 0x7Fu), longest, rcp);
+  C.lam[j] = lam;
+  if constexpr (DIR == kFwd) gen_push<W>(C, d, arc, f, lam);
+  else gen_bstep<W>(C, d, lo, hi, lam);
 }
 
 // The same for a variable in two rows whose levels are regular: both layers in one lane (their links
@@ -241,6 +258,106 @@ __device__ __forceinline__ void pair_step(const Cell &C, uint32_t d, float2 l, f
   }
 }
 
+// The cell's chunk records, 64 of them in a register, one per lane, so that a chunk's bounds cost a
+// lane read instead of a round trip to memory.
+template <int DIR>
+struct Work {
+  const uint32_t *work;
+  int nw, lane, base = -64;
+  uint32_t win = 0u;
+  __device__ __forceinline__ uint32_t at(int i) {  // i-th chunk in pass order
+    const int q = DIR == kFwd ? min(i, nw - 1) : max(nw - 1 - i, 0);
+    if (uint32_t(q - base) >= 64u) {
+      base = DIR == kFwd ? q : max(q - 63, 0);
+      win = work[min(base + lane, nw - 1)];
+      // waits here: where the paths meet again the compiler would wait for every load in flight
+      asm volatile("" : "+v"(win));
+    }
+    return uint32_t(__builtin_amdgcn_readlane(int(win), q - base));
+  }
+};
+__device__ __forceinline__ int chunk_count(uint32_t r) { return int((r >> 13) & 0x3FFu); }
+__device__ __forceinline__ int chunk_longest(uint32_t r) { return int(r >> 28) == 15 ? -1 : int(r >> 28); }
+
+// A layer's messages in a kCellGen cell: its own nodes' forward ones, and what their arcs carry. wide:
+// more than two nodes.
+__device__ __forceinline__ void take_f(const Cell &C, u32x4 d, bool wide, float *f) {
+  const int p = int(d[0] & 0x7FFFu);
+  const float2 a = C.X[p];
+  f[0] = a.x;
+  f[1] = a.y;
+  if (wide) {
+    const float2 b = C.X[p + 1];
+    f[2] = b.x;
+    f[3] = b.y;
+  }
+}
+__device__ __forceinline__ void take_arcs(const Cell &C, Arcs arc, bool wide, float *lo, float *hi) {
+  const float *x = reinterpret_cast<const float *>(C.X);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    lo[u] = x[arc.lo(u)];
+    hi[u] = x[arc.hi(u)];
+  }
+  if (wide) {
+#pragma unroll
+    for (int u = 2; u < 4; ++u) {
+      lo[u] = x[arc.lo(u)];
+      hi[u] = x[arc.hi(u)];
+    }
+  }
+}
+
+// One update pass of a kCellGen cell. Its descriptors stay in global memory (the cells are large and
+// few, so LDS goes to messages): read two chunks ahead. The multipliers and the pass's standing messages
+// (forward: behind the arcs, backward: the own nodes') are read one chunk ahead, as in cell_pass. Two
+// slots take turns, so that nothing in flight is moved between registers (a move waits for the load).
+template <int BLOCK, int DIR>
+__device__ __forceinline__ void gen_pass(const Cell &C) {
+  const int tid = int(threadIdx.x), nw = C.nwork;
+  const float rcp = 1.0f / float((tid & 63) + 1);
+  Work<DIR> work{C.work, nw, tid & 63};
+  struct Slot {
+    uint32_t r;
+    u32x4 d;
+    Arcs arc;
+    float lam, f[4], lo[4], hi[4];
+  };
+  auto pos = [&](uint32_t r) { return min(int(r & 0x1FFFu) + tid, C.nl - 1); };
+  auto wide = [](uint32_t r) { return ((r >> 24) & 3u) > 1u; };
+  auto fetch = [&](Slot &s, int i) {
+    s.r = work.at(i);
+    s.d = C.ga[pos(s.r)];
+    s.arc.a = C.gb[pos(s.r)];
+  };
+  auto standing = [&](Slot &s) {
+    s.lam = C.lam[pos(s.r)];
+    if (DIR == kFwd) take_arcs(C, s.arc, wide(s.r), s.lo, s.hi);
+    else take_f(C, s.d, wide(s.r), s.f);
+  };
+  auto step = [&](Slot &s, Slot &next, int i) {
+    if (DIR == kFwd) take_f(C, s.d, wide(s.r), s.f);
+    else take_arcs(C, s.arc, wide(s.r), s.lo, s.hi);
+    standing(next);
+    if (tid < chunk_count(s.r) && (s.d[2] & 0x7Fu)) {
+      const int j = pos(s.r);
+      if (wide(s.r)) gen_step<DIR, 4>(C, s.d, s.arc, s.lam, s.f, s.lo, s.hi, j, chunk_longest(s.r), rcp);
+      else gen_step<DIR, 2>(C, s.d, s.arc, s.lam, s.f, s.lo, s.hi, j, chunk_longest(s.r), rcp);
+    }
+    const bool ends = BLOCK == 64 || (s.r & (DIR == kFwd ? kCellStepEnd : kCellStepBegin));
+    fetch(s, i + 2);
+    if (ends) step_sync<BLOCK>();
+  };
+  Slot a, b;
+  fetch(a, 0);
+  fetch(b, 1);
+  standing(a);
+  for (int i = 0; i < nw; i += 2) {
+    step(a, b, i);
+    if (i + 1 < nw) step(b, a, i + 1);
+  }
+}
+
 // One update pass in direction DIR over the cell's chunks (up to BLOCK layers, or variables of
 // kCellPair, of one step). Reads that the chunk before does not write are issued ahead of its work:
 // the descriptors two chunks ahead, the multipliers and the pass's standing messages (a forward
@@ -248,6 +365,10 @@ __device__ __forceinline__ void pair_step(const Cell &C, uint32_t d, float2 l, f
 // within the cell's LDS (it ends in slack) and writes nothing.
 template <int BLOCK, int DIR, int KIND>
 __device__ __forceinline__ void cell_pass(const Cell &C) {
+  if constexpr (KIND == kCellGen) {
+    gen_pass<BLOCK, DIR>(C);
+    return;
+  } else {
   constexpr bool kPair = KIND == kCellPair;
   using Own = std::conditional_t<kPair, float4, float2>;
   using Lam = std::conditional_t<kPair, float2, float>;
@@ -256,18 +377,7 @@ __device__ __forceinline__ void cell_pass(const Cell &C) {
   };
   const int tid = int(threadIdx.x), nw = C.nwork;
   const float rcp = kPair ? 0.0f : 1.0f / float((tid & 63) + 1);
-  // chunk records: 64 of them in a register, one per lane, so that a chunk's bounds cost a lane read
-  // instead of a round trip to memory
-  int base = -64;
-  uint32_t win = 0u;
-  auto record = [&](int i) {  // i-th chunk in pass order
-    const int q = DIR == kFwd ? min(i, nw - 1) : max(nw - 1 - i, 0);
-    if (uint32_t(q - base) >= 64u) {
-      base = DIR == kFwd ? q : max(q - 63, 0);
-      win = C.work[min(base + (tid & 63), nw - 1)];
-    }
-    return uint32_t(__builtin_amdgcn_readlane(int(win), q - base));
-  };
+  Work<DIR> work{C.work, nw, tid & 63};
   auto pos = [&](uint32_t r) { return int(r & 0x1FFFu) + tid; };
   // a descriptor leads to an area, so past the cell's end the last one is read again
   const int last = C.nl / (kPair ? 2 : 1) - 1;
@@ -278,7 +388,7 @@ __device__ __forceinline__ void cell_pass(const Cell &C) {
     x.b = kPair ? C.X[(d >> 16) & 0x7FFFu] : x.a;
     return x;
   };
-  uint32_t r0 = record(0), r1 = record(1);
+  uint32_t r0 = work.at(0), r1 = work.at(1);
   uint32_t da = desc(r0), db = desc(r1), ea = 0u;
   Lam la = reinterpret_cast<const Lam *>(C.lam)[pos(r0)];
   if (!kPair) ea = C.w1[pos(r0)];
@@ -287,7 +397,7 @@ __device__ __forceinline__ void cell_pass(const Cell &C) {
   if (DIR == kFwd) oa = reinterpret_cast<const Own *>(C.X)[pos(r0)];
   else fa = far(da);
   for (int i = 0; i < nw; ++i) {
-    const uint32_t r2 = record(i + 2);
+    const uint32_t r2 = work.at(i + 2);
     // what the pass itself wrote: a forward pass its parents' links, a backward pass its own
     if (DIR == kFwd) fa = far(da);
     else oa = reinterpret_cast<const Own *>(C.X)[pos(r0)];
@@ -298,14 +408,13 @@ __device__ __forceinline__ void cell_pass(const Cell &C) {
     Far fb{};
     if (DIR == kFwd) ob = reinterpret_cast<const Own *>(C.X)[pos(r1)];
     else fb = far(db);
-    if (tid < int((r0 >> 13) & 0x3FFu)) {
+    if (tid < chunk_count(r0)) {
       if constexpr (kPair) {
         if (r0 & kCellTakes) pair_step<DIR, 0>(C, da, la, fa.a, fa.b, oa, pos(r0));
         else if (r0 & kCellCounts) pair_step<DIR, 1>(C, da, la, fa.a, fa.b, oa, pos(r0));
         else pair_step<DIR, 2>(C, da, la, fa.a, fa.b, oa, pos(r0));
       } else if (ea & 0x7Fu) {  // not a pad
-        layer_step<DIR, KIND == kCellGen>(C, da, ea, la, fa.a, oa, pos(r0), (r0 & kCellRegular) != 0u,
-                                             int(r0 >> 28) == 15 ? -1 : int(r0 >> 28), rcp);
+        layer_step<DIR>(C, da, ea, la, fa.a, oa, pos(r0), (r0 & kCellRegular) != 0u, chunk_longest(r0), rcp);
       }
     }
     // the next step reads what this one wrote
@@ -319,6 +428,7 @@ __device__ __forceinline__ void cell_pass(const Cell &C) {
     oa = ob;
     fa = fb;
   }
+  }
 }
 
 // The messages that direction DIR's pass leaves under the current multipliers (no update): rows are
@@ -329,28 +439,42 @@ template <int BLOCK, int DIR, int KIND>
 __device__ __forceinline__ void cell_sweep(const Cell &C, int bwp) {
   constexpr bool kPair = KIND == kCellPair;
   static_assert(!kPair || DIR == kBwd, "two-row stages sweep backward");
-  auto w0 = [&](int j) { return kPair ? uint32_t(reinterpret_cast<const uint16_t *>(C.w0)[j]) : C.w0[j]; };
   for (int k = int(threadIdx.x); k < C.nrow; k += BLOCK) {
     const uint32_t r = C.row[k];
     int j = int(DIR == kFwd ? r & 0x1FFFu : (r >> 13) & 0x1FFFu);
     const int end = int(DIR == kFwd ? (r >> 13) & 0x1FFFu : r & 0x1FFFu);
-    uint32_t d0 = w0(j), d1 = kPair ? 0u : C.w1[j];
-    float lam = C.lam[j];
-    float2 m = DIR == kFwd ? C.X[C.nl + k * bwp] : C.X[j];
-    while (j != end) {
-      const int p = int(d0 & 0x7FFFu);
-      if (KIND == kCellGen && (d1 & kCellGeneral)) {
-        const uint4 g = C.grec[d1 >> 16];
-        if (DIR == kFwd) general_push(C, g, p, lam);
-        else general_bstep(C, g, p, lam);
-        const int own = int(g.z);
-        j = int(DIR == kFwd ? d0 >> 16 : g.y >> 16);
-        m = DIR == kFwd ? C.X[own] : C.X[j];  // used by a narrow neighbour, whose link is its index
-        d0 = w0(j);
-        d1 = C.w1[j];
-        lam = C.lam[j];
-      } else {
-        const int nx = DIR == kFwd ? int(d0 >> 16) : p;  // a narrow layer's parent's link is its index
+    if constexpr (KIND == kCellGen) {
+      u32x4 d = C.ga[j];
+      Arcs arc{C.gb[j]};
+      while (j != end) {
+        const int nx = int(DIR == kFwd ? d[1] & 0xFFFFu : d[1] >> 16);
+        const u32x4 nd = C.ga[nx];
+        const Arcs na{C.gb[nx]};
+        const float lam = C.lam[j];
+        const bool wide = ((d[2] >> 16) & 7u) > 2u;
+        if (DIR == kFwd) {
+          float f[4];
+          take_f(C, d, wide, f);
+          if (wide) gen_push<4>(C, d, arc, f, lam);
+          else gen_push<2>(C, d, arc, f, lam);
+        } else {
+          float lo[4], hi[4];
+          take_arcs(C, arc, wide, lo, hi);
+          if (wide) gen_bstep<4>(C, d, lo, hi, lam);
+          else gen_bstep<2>(C, d, lo, hi, lam);
+        }
+        j = nx;
+        d = nd;
+        arc = na;
+      }
+    } else {
+      auto w0 = [&](int q) { return kPair ? uint32_t(reinterpret_cast<const uint16_t *>(C.w0)[q]) : C.w0[q]; };
+      uint32_t d0 = w0(j), d1 = kPair ? 0u : C.w1[j];
+      float lam = C.lam[j];
+      float2 m = DIR == kFwd ? C.X[C.nl + k * bwp] : C.X[j];
+      while (j != end) {
+        const int p = int(d0 & 0x7FFFu);
+        const int nx = DIR == kFwd ? int(d0 >> 16) : p;  // the parent's link is the parent's index
         const uint32_t n0 = w0(nx), n1 = kPair ? 0u : C.w1[nx];
         const float nlam = C.lam[nx];
         if constexpr (kPair) {
@@ -378,7 +502,7 @@ __global__ __launch_bounds__(BLOCK) void cell_kernel(const Dev D, const CellArgs
                                                      const int n) {
   extern __shared__ __align__(16) char lds[];
   const int cell = xcd_tile(int(blockIdx.x), int(gridDim.x));
-  const int4 r0 = A.rec[4 * cell], r1 = A.rec[4 * cell + 1], r2 = A.rec[4 * cell + 2], r3 = A.rec[4 * cell + 3];
+  const int4 r0 = A.rec[3 * cell], r1 = A.rec[3 * cell + 1], r2 = A.rec[3 * cell + 2];
   const int nl = r0.x, tid = int(threadIdx.x);
   const int bw = KIND == kCellGen ? A.bw : 2;  // narrow stages have narrow boundaries
   const int32_t *layer = A.layer + r1.x;
@@ -391,12 +515,13 @@ __global__ __launch_bounds__(BLOCK) void cell_kernel(const Dev D, const CellArgs
   C.nl = nl;
   C.work = A.work + r0.w;
   C.X = reinterpret_cast<float2 *>(lds);
-  C.grec = reinterpret_cast<uint4 *>(C.X + r1.z);
-  C.lam = reinterpret_cast<float *>(C.grec + r2.z);
+  C.lam = reinterpret_cast<float *>(C.X + r1.z);
   C.w0 = reinterpret_cast<uint32_t *>(C.lam + nl);
   C.w1 = C.w0 + nl;
-  C.row = kPair ? C.w0 + nl / 2 : C.w1 + nl;
-  C.garc = C.row + C.nrow;
+  C.row = kPair ? C.w0 + nl / 2 : (KIND == kCellGen ? C.w0 : C.w1 + nl);
+  C.ga = A.ga + r0.z;
+  C.gb = A.gb + r0.z;
+  C.consts = 2 * (r1.z - 2);  // the last areas are the constants' (and one to keep the count even)
 
   // prologue: the program (shared by cells of equal structure, so it comes from cache), the
   // multipliers, and per row part the messages it starts from; every load that needs no other is
@@ -437,7 +562,7 @@ __global__ __launch_bounds__(BLOCK) void cell_kernel(const Dev D, const CellArgs
         for (int t = 0; t < Q; ++t) a[t] = reinterpret_cast<const uint2 *>(A.w0 + r0.z / 2)[q[t]];
 #pragma unroll
         for (int t = 0; t < Q; ++t) reinterpret_cast<uint2 *>(C.w0)[q[t]] = a[t];
-      } else {
+      } else if constexpr (KIND == kCellLayers) {
         u32x4 a[Q], c[Q];
 #pragma unroll
         for (int t = 0; t < Q; ++t) {
@@ -454,10 +579,7 @@ __global__ __launch_bounds__(BLOCK) void cell_kernel(const Dev D, const CellArgs
       for (int t = 0; t < Q; ++t) reinterpret_cast<float4 *>(C.lam)[q[t]] = l[t];
     }
   }
-  if constexpr (KIND == kCellGen) {
-    for (int q = tid; q < r2.z; q += BLOCK) C.grec[q] = A.grec[r2.w + q];
-    for (int q = tid; q < r3.x; q += BLOCK) C.garc[q] = A.garc[r3.y + q];
-  }
+  if (KIND == kCellGen && tid == 0) C.X[r1.z - 2] = make_float2(0.0f, INFINITY);
   for (int k = tid; k < C.nrow; k += BLOCK) {
     const uint32_t r = k == tid ? row0 : A.row[r2.y + k];
     C.row[k] = r;
@@ -466,13 +588,10 @@ __global__ __launch_bounds__(BLOCK) void cell_kernel(const Dev D, const CellArgs
     const int top = nl + k * bwp;  // the link above the first level; fw, bc: floats of it and of the last level's
     int fw = 2, ba = je, bc = 2;
     if constexpr (KIND == kCellGen) {
-      const uint32_t xb = A.w1[r0.z + jb], xe = A.w1[r0.z + je];
-      if (xb & kCellGeneral) fw = max(2, int(A.grec[r2.w + int(xb >> 16)].y & 0xFu));
-      if (xe & kCellGeneral) {
-        const uint4 g = A.grec[r2.w + int(xe >> 16)];
-        ba = int(g.z);
-        bc = max(2, int((g.y >> 4) & 0xFu));
-      }
+      const u32x4 xb = C.ga[jb], xe = C.ga[je];
+      fw = max(2, int((xb[2] >> 16) & 7u));
+      ba = int(xe[0] >> 16);
+      bc = max(2, int((xe[2] >> 20) & 7u));
     }
     float2 fi = make_float2(0.0f, INFINITY);
     float2 bi = make_float2((r & kCellRowTermX) ? 0.0f : INFINITY, (r & kCellRowTermY) ? 0.0f : INFINITY);
@@ -481,7 +600,9 @@ __global__ __launch_bounds__(BLOCK) void cell_kernel(const Dev D, const CellArgs
       if (!(r & kCellRowLast)) {
         const int L = layer[je];
         src = D.mbc + (KIND == kCellGen && D.grec ? D.grec[L].y : 2 * L);
-        bi = *reinterpret_cast<const float2 *>(src);
+        // (areas of wide levels may start at any float)
+        if (KIND == kCellGen) bi = make_float2(src[0], src[1]);
+        else bi = *reinterpret_cast<const float2 *>(src);
       }
     } else if constexpr (PROG != kCellWhole) {
       const float2 m = k == tid ? in0 : *reinterpret_cast<const float2 *>(in);
@@ -513,8 +634,10 @@ __global__ __launch_bounds__(BLOCK) void cell_kernel(const Dev D, const CellArgs
 
   // a forward pass leaves pushes on the links below last levels too: their terminals' values again
   auto terminals = [&] {
+    if (KIND == kCellGen) return;
     for (int k = tid; k < C.nrow; k += BLOCK) {
       const uint32_t r = C.row[k];
+      // (kCellGen: its arcs name the terminals themselves)
       if (r & kCellRowLast)
         C.X[(r >> 13) & 0x1FFFu] = make_float2((r & kCellRowTermX) ? 0.0f : INFINITY, (r & kCellRowTermY) ? 0.0f : INFINITY);
     }
@@ -557,7 +680,7 @@ __global__ __launch_bounds__(BLOCK) void cell_kernel(const Dev D, const CellArgs
       int from = nl + k * bwp;
       if (kPush) {
         from = int((C.row[k] >> 13) & 0x1FFFu);
-        if (KIND == kCellGen && (C.w1[from] & kCellGeneral)) from = int(C.grec[C.w1[from] >> 16].z);
+        if (KIND == kCellGen) from = int(C.ga[from][0] >> 16);
       }
       float2 *out = reinterpret_cast<float2 *>(A.out + size_t(to) * size_t(bw));
       out[0] = C.X[from];
@@ -573,15 +696,14 @@ __global__ __launch_bounds__(BLOCK) void cell_kernel(const Dev D, const CellArgs
     const int L = layer[q];
     if (L < 0) continue;
     D.lam[L] = C.lam[q];
-    const uint32_t d1 = A.w1[r0.z + q];
-    if (d1 & kCellLast) continue;
-    if (KIND == kCellGen && (d1 & kCellGeneral)) {
-      const uint4 g = C.grec[d1 >> 16];
-      const float *bp = reinterpret_cast<const float *>(C.X + g.z);
-      float *to = D.mbc + D.grec[L].y;
-      for (int u = 0; u < int((g.y >> 4) & 0xFu); ++u) to[u] = bp[u];
+    if constexpr (KIND == kCellGen) {
+      const u32x4 d = C.ga[q];
+      if (d[2] & kCellLast) continue;
+      const float *bp = reinterpret_cast<const float *>(C.X + (d[0] >> 16));
+      float *to = D.mbc + (D.grec ? D.grec[L].y : 2 * L);
+      for (int u = 0; u < int((d[2] >> 20) & 7u); ++u) to[u] = bp[u];
     } else {
-      *reinterpret_cast<float2 *>(D.mbc + 2 * L) = C.X[q];
+      if (!(A.w1[r0.z + q] & kCellLast)) *reinterpret_cast<float2 *>(D.mbc + 2 * L) = C.X[q];
     }
   }
 }

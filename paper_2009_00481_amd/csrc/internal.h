@@ -63,24 +63,29 @@ constexpr uint32_t kInArcHi = 0x8000u;
 
 // Cells (cells.cpp, cells.hip). A local layer's descriptors: h = area of its parent's link (bits 0-14)
 // | kCellCount; w0 = h | child layer << 16 (kCellPair: h of the variable's two layers in one word);
-// w1 = rows of its variable (bits 0-6, 0 for a pad), position among them (7-13), kCellGeneral,
-// kCellLast, and in bits 16-31 the arcs of a narrow layer or the record of a general one. Areas are
-// pairs of floats.
-constexpr uint32_t kCellCount = 1u << 15, kCellPosShift = 7, kCellGeneral = 1u << 14, kCellLast = 1u << 15;
+// w1 = rows of its variable (bits 0-6, 0 for a pad), position among them (7-13), kCellLast, and in bits
+// 16-31 the arcs of a narrow layer. kCellGen has four words instead: area of the parent's link | area
+// of its own << 16, child layer | parent layer << 16 (0xFFFF: not in the cell), w1 with the nodes of its
+// level in bits 16-19 and of its child level in bits 20-23, 0; and four for the arcs: per node the
+// float of X behind its 0-arc | 1-arc << 16. Areas are pairs of floats; a kCellGen cell's last but one
+// holds the constants 0 and +inf.
+constexpr uint32_t kCellCount = 1u << 15, kCellPosShift = 7, kCellLast = 1u << 15;
 // row part: first (bits 0-12) and last (13-25) local layer, whether it starts at the row's root and
 // ends at its last level, and the values behind that level's virtual nodes 0 and 1 (0 if set, else
 // +inf)
 constexpr uint32_t kCellRowRoot = 1u << 26, kCellRowLast = 1u << 27, kCellRowTermX = 1u << 28, kCellRowTermY = 1u << 29;
 // chunk of a step: first layer, or variable of kCellPair (bits 0-12), their number (13-22), whether
-// every level is regular, all of them taking / counting, whether the chunk begins / ends its step, and
+// every level is regular, all of them taking / counting (kCellGen: the most nodes of a level less one in
+// bits 24-25 instead), whether the chunk begins / ends its step, and
 // the most rows of a variable less one (bits 28-31, 15: 16 or more)
 constexpr uint32_t kCellRegular = 1u << 23, kCellTakes = 1u << 24, kCellCounts = 1u << 25;
 constexpr uint32_t kCellStepBegin = 1u << 26, kCellStepEnd = 1u << 27;
-// kernel variants: one layer per lane (narrow levels only, or any), one two-row variable per lane
+// kernel variants: one layer per lane (narrow levels only, or up to four nodes), one two-row variable
+// per lane
 constexpr int kCellLayers = 0, kCellGen = 1, kCellPair = 2;
-// limits: rows of a variable (one wavefront), nodes of a level (a lane loops over them), layers of a
+// limits: rows of a variable (one wavefront), nodes of a level (one arc record), layers of a
 // cell, bytes of LDS of a component (estimate) and of a cell
-constexpr int kCellMaxRows = 64, kCellMaxWidth = 8, kCellMaxLayers = 8188;
+constexpr int kCellMaxRows = 64, kCellMaxWidth = 4, kCellMaxLayers = 8188;
 constexpr int kCellLdsMax = 140 << 10, kCellLdsCap = 160 << 10;
 
 // Records bddmp_last_error's message and returns code.
@@ -123,7 +128,7 @@ struct ArenaLayout {
   size_t d_fresh, mbuf, xbuf, part, root_e, cut_part, lb_hist, scal;
   size_t inst_row, inst_lb;
   size_t cuts, cut_slots, cut_live, cut_rb, cut_arc, mu_in, dfw, dbw, cut_e, inst_cut, inst_cut_idx, exit_rec;
-  size_t c_rec[2], c_work[2], c_w0[2], c_w1[2], c_row[2], c_grec[2], c_garc[2], c_layer[2], c_link[2], c_term[2];
+  size_t c_rec[2], c_work[2], c_w0[2], c_w1[2], c_row[2], c_ga[2], c_gb[2], c_layer[2], c_link[2], c_term[2];
   size_t c_lam[2], c_in[2];
   size_t total;
 };
@@ -141,15 +146,12 @@ struct WaveRange {
 struct CellStage {
   int32_t n_cells = 0, block = 64, lds = 0, kind = 0;  // workgroup lanes, bytes of LDS, kernel variant
   int32_t bw = 2;                                      // floats of a boundary message (even)
-  // 16 per cell: layers, chunks, bases of w0 / w1 and work; base in cell order (lamc, layer), first
-  // global row part, areas, 0; row parts and their base, general layers and their base; arcs of those
-  // and their base; 0, 0
+  // 12 per cell: layers, chunks, bases of the descriptors and of work; base in cell order (lamc, layer),
+  // first global row part, areas, 0; row parts and their base, 0, 0
   std::vector<int32_t> rec;
   std::vector<uint32_t> work;           // chunks in forward order
   std::vector<uint32_t> w0, w1, row;    // per local layer (w0 of kCellPair: per two), per row part
-  // 4 per general layer: first arc | child layer << 16, own | child width << 4 | parent layer << 16, area
-  // of its link, 0 (0xFFFF: no such layer in the cell)
-  std::vector<uint32_t> grec, garc;
+  std::vector<uint32_t> ga, gb;         // kCellGen: descriptors and arcs, 4 words per local layer each
   std::vector<int32_t> layer;           // cell order: storage layer, -1 for a pad
   std::vector<int32_t> link, term;      // per global row part: the partner's in the other stage, the bound term (-1: none)
 };

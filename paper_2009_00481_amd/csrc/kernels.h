@@ -149,8 +149,7 @@ struct CellArgs {
   const int4 *rec;
   const uint32_t *work;
   const uint32_t *w0, *w1, *row;
-  const uint4 *grec;
-  const uint32_t *garc;
+  const uint32_t __attribute__((ext_vector_type(4))) *ga, *gb;
   const int32_t *layer, *link, *term;
   float *lamc;       // multipliers in cell order
   const float *in;   // messages coming in at this stage's row parts, bw floats each

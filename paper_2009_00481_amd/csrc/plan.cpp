@@ -1475,8 +1475,8 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
     A.c_w0[q] = take(4 * C.w0.size());
     A.c_w1[q] = take(4 * C.w1.size());
     A.c_row[q] = take(4 * C.row.size());
-    A.c_grec[q] = take(4 * C.grec.size());
-    A.c_garc[q] = take(4 * C.garc.size());
+    A.c_ga[q] = take(4 * C.ga.size());
+    A.c_gb[q] = take(4 * C.gb.size());
     A.c_layer[q] = take(4 * C.layer.size());
     A.c_link[q] = take(4 * C.link.size());
     A.c_term[q] = take(4 * C.term.size());

@@ -459,8 +459,8 @@ int32_t solver_bind(const Plan &P, void *arena, size_t bytes, void *stream, Solv
     c.w0 = reinterpret_cast<const uint32_t *>(b + A.c_w0[q]);
     c.w1 = reinterpret_cast<const uint32_t *>(b + A.c_w1[q]);
     c.row = reinterpret_cast<const uint32_t *>(b + A.c_row[q]);
-    c.grec = reinterpret_cast<const uint4 *>(b + A.c_grec[q]);
-    c.garc = reinterpret_cast<const uint32_t *>(b + A.c_garc[q]);
+    c.ga = reinterpret_cast<decltype(c.ga)>(b + A.c_ga[q]);
+    c.gb = reinterpret_cast<decltype(c.gb)>(b + A.c_gb[q]);
     c.layer = reinterpret_cast<const int32_t *>(b + A.c_layer[q]);
     c.link = reinterpret_cast<const int32_t *>(b + A.c_link[q]);
     c.term = reinterpret_cast<const int32_t *>(b + A.c_term[q]);
@@ -539,8 +539,8 @@ int32_t solver_bind(const Plan &P, void *arena, size_t bytes, void *stream, Solv
     auto bytes = [](const auto &v) { return std::make_pair(static_cast<const void *>(v.data()), 4 * v.size()); };
     const std::pair<size_t, std::pair<const void *, size_t>> arrays[] = {
         {A.c_rec[q], bytes(c.rec)},     {A.c_work[q], bytes(c.work)},   {A.c_w0[q], bytes(c.w0)},
-        {A.c_w1[q], bytes(c.w1)},       {A.c_row[q], bytes(c.row)},     {A.c_grec[q], bytes(c.grec)},
-        {A.c_garc[q], bytes(c.garc)},   {A.c_layer[q], bytes(c.layer)}, {A.c_link[q], bytes(c.link)},
+        {A.c_w1[q], bytes(c.w1)},       {A.c_row[q], bytes(c.row)},     {A.c_ga[q], bytes(c.ga)},
+        {A.c_gb[q], bytes(c.gb)},       {A.c_layer[q], bytes(c.layer)}, {A.c_link[q], bytes(c.link)},
         {A.c_term[q], bytes(c.term)}};
     for (const auto &a : arrays)
       if (const hipError_t e = up(a.first, a.second.first, a.second.second); e != hipSuccess) {

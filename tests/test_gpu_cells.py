@@ -1,7 +1,8 @@
 """GPU tests of the cell launches (the default launch form's iterations where the plan's components fit
 a workgroup): multipliers, bounds, min-marginals, per-instance bounds and every later call bitwise
 equal to host-launched waves, at the edges of the cells' forms: one stage and two, one-wavefront and
-large cells, two-row variables and others, variables in up to 64 rows, levels of up to 8 nodes, rings
+large cells, two-row variables and others, variables in up to 64 rows, levels of up to 4 nodes (wider
+ones run as waves), rings
 of bound terms longer and shorter than the run."""
 import numpy as np
 import pytest
@@ -23,11 +24,11 @@ def _star(m, k, seed):
     return I.from_rows(n, rng.standard_normal(n, dtype=np.float32).astype(np.float64), rows)
 
 
-def _wide(m, k, seed):
-    """Chains of knapsack rows with coefficients up to 4 (levels of 3 to 8 nodes)."""
+def _wide(m, k, most, seed):
+    """Chains of knapsack rows with coefficients up to 3 (levels of up to most + 1 nodes)."""
     rng = np.random.default_rng(seed)
     n = m * (k - 1) + 1
-    rows = [(np.arange(j * (k - 1), j * (k - 1) + k), rng.integers(1, 4, k), 1, 7) for j in range(m)]
+    rows = [(np.arange(j * (k - 1), j * (k - 1) + k), rng.integers(1, 4, k), 1, most) for j in range(m)]
     return I.from_rows(n, rng.standard_normal(n, dtype=np.float32).astype(np.float64), rows)
 
 
@@ -42,9 +43,12 @@ CASES = {
     "star16": lambda: [_star(16, 3, 6)],
     "star17": lambda: [_star(17, 2, 7)],
     "star64": lambda: [_star(64, 2, 8)],
-    "wide": lambda: [_wide(40, 5, 9)],
+    "wide4": lambda: [_wide(40, 5, 3, 9)],
+    "wide4_long": lambda: [_wide(6, 300, 3, 12)],
+    "wide12": lambda: [_wide(40, 9, 11, 9)],
     "tracking200": lambda: [I.tracking(200, seed=10)],
     "tracking1400": lambda: [I.tracking(1400, seed=11)],
+    "tracking1800": lambda: [I.tracking(1800, seed=13)],
     "tracking_batch": lambda: [I.tracking(200 + 150 * k, seed=k) for k in range(6)],
     "potts_and_tracking": lambda: [I.potts_grid(20, 30, 4, seed=1), I.tracking(300, seed=2), I.config(1)],
 }
