@@ -597,15 +597,9 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
       __syncthreads();
       if (active && pos == 0) {
         // J_i sum in ascending row order (the segment is sorted by row)
-        float sum = 0.0f;
-        int nf = 0;
-        for (int q = 0; q < len; ++q) {
-          const float dq = s_d[s + q];
-          if (isinf(dq)) ++nf;
-          else sum += dq;
-        }
-        s_share[s] = nf ? sum / float(nf) : sum / float(len);
-        s_nf[s] = nf;
+        const RowSum r = row_sum(s_d + s, len);
+        s_share[s] = r.sum / float(r.nf ? r.nf : len);
+        s_nf[s] = r.nf;
       }
       __syncthreads();
       if (active) {
@@ -986,15 +980,9 @@ void group_pair_kernel(const Dev D, const GroupArgs A) {
   for (int k = 0; k < 2; ++k)
     if (act[k] && pos[k] == 0) {
       // J_i sum in ascending row order (the segment is sorted by row)
-      float sum = 0.0f;
-      int nf = 0;
-      for (int q = 0; q < len[k]; ++q) {
-        const float dq = p_d[k][s + q];
-        if (isinf(dq)) ++nf;
-        else sum += dq;
-      }
-      p_share[k][s] = nf ? sum / float(nf) : sum / float(len[k]);
-      p_nf[k][s] = nf;
+      const RowSum r = row_sum(&p_d[k][s], len[k]);
+      p_share[k][s] = r.sum / float(r.nf ? r.nf : len[k]);
+      p_nf[k][s] = r.nf;
     }
   __syncthreads();
 #pragma unroll
@@ -1043,14 +1031,9 @@ __global__ __launch_bounds__(kTile) void wave_big_kernel(const Dev D, const int 
   if (MODE == kUpdate) {
     __syncthreads();
     if (threadIdx.x == 0) {
-      float sum = 0.0f;
-      int nf = 0;
-      for (int q = 0; q < cnt; ++q) {
-        if (isinf(s_d[q])) ++nf;
-        else sum += s_d[q];
-      }
-      s_share = nf ? sum / float(nf) : sum / float(cnt);
-      s_nf = nf;
+      const RowSum r = row_sum(s_d, cnt);
+      s_share = r.sum / float(r.nf ? r.nf : cnt);
+      s_nf = r.nf;
     }
     __syncthreads();
   }

@@ -100,24 +100,17 @@ __device__ __forceinline__ Seg seg_update(float d, uint32_t meta, bool active, f
   const int pos = int((meta >> kMetaPosShift) & kMetaField);
   const int len = int((meta >> kMetaLenShift) & kMetaField);
   if (active && pos == 0) {
-    float sum = 0.0f, moved = 0.0f;
-    int nf = 0, neg = 0;
-    for (int q = 0; q < len; ++q) {
-      const float dq = s_d[s + q];
-      if (isinf(dq)) {
-        ++nf;
-        if (dq < 0.0f) neg = 1;
-      } else {
-        sum += dq;
-      }
+    RowSum r = row_sum(s_d + s, len);
+    int neg = 0;
+    if (r.nf) {
+      for (int q = 0; q < len; ++q)
+        if (isinf(s_d[s + q]) && s_d[s + q] < 0.0f) neg = 1;
+      r.sum = 0.0f;
+      for (int q = 0; q < len; ++q)
+        if (moving(s_d[s + q], neg)) r.sum += s_d[s + q];
     }
-    if (nf)
-      for (int q = 0; q < len; ++q) {
-        const float dq = s_d[s + q];
-        if (moving(dq, neg)) moved += dq;
-      }
-    s_share[s] = nf ? moved / float(nf) : sum / float(len);
-    s_nf[s] = nf | (neg << 30);
+    s_share[s] = r.sum / float(r.nf ? r.nf : len);
+    s_nf[s] = r.nf | (neg << 30);
   }
   __syncthreads();
   const int h = s - pos;

@@ -1,0 +1,40 @@
+"""GPU tests of the wave kernels' tiles at the edges of their forms, bitwise against the oracle's float
+mirror: the exchange sum of variables in few to many rows (blocks of eight and four rows, a workgroup's
+tile and more), rows that force the variable among them."""
+import numpy as np
+import pytest
+
+from oracle import Oracle
+from paper_2009_00481_amd import binding as B
+from paper_2009_00481_amd import instances as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(ilp, T, **opt):
+    plan = B.Plan(B.Problem.from_ilp(ilp), **opt)
+    s = B.Solver(plan)
+    s.set_graphs(False)
+    s.iterate(T)
+    m0, m1 = s.min_marginals()
+    o = Oracle(I.ILP(ilp.n, ilp.cost, ilp.row_ptr, ilp.col, ilp.coef, ilp.sense, ilp.rhs, plan.order()), precision="f32")
+    o.init()
+    o.iterate(T)
+    r0, r1 = o.min_marginals()
+    for got, want in ((s.get_lambda(), o.lam()), (m0, r0), (m1, r1)):
+        assert np.array_equal(got.cpu().numpy().astype(np.float64), np.asarray(want, np.float64))
+
+
+@pytest.mark.parametrize("forced", [0, 3])
+@pytest.mark.parametrize("m", [1, 3, 4, 5, 7, 8, 9, 12, 13, 45, 64, 65, 200, 256, 257, 300])
+def test_exchange_sums_bitwise(m, forced):
+    """m rows share variable 0; forced of them more hold it at 0 (one-variable rows: infinite differences)."""
+    rng = np.random.default_rng([m, forced])
+    rows = []
+    for j in range(m):
+        v = np.array([0, 1 + 2 * j, 2 + 2 * j])
+        rows.append((v, rng.choice([-1, 1], 3), int(rng.integers(1, 3)), 0))
+    for j in range(forced):
+        rows.insert(int(rng.integers(0, len(rows) + 1)), (np.array([0]), np.array([1]), 1, 0))
+    n = 1 + 2 * m
+    _check(I.from_rows(n, rng.standard_normal(n, dtype=np.float32).astype(np.float64), rows), 3)
