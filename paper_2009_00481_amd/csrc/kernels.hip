@@ -382,6 +382,12 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
   const bool flat = !NARROW_ONLY && gtr.x >= 0;
   const bool map_lane = flat && 16 * s < (gtr.y & 0xFFFF) + int(uint32_t(gtr.y) >> 16);
   uint4 gmp = make_uint4(0u, 0u, 0u, 0u);
+  uint32_t gword = 0u;  // the layer's word behind the node maps
+  if constexpr (!NARROW_ONLY)
+    if (flat && active) {
+      const int nodes = (gtr.y & 0xFFFF) + int(uint32_t(gtr.y) >> 16);
+      gword = reinterpret_cast<const uint32_t *>((DIR == kFwd ? D.fgm : D.bgm) + gtr.x + ((nodes + 15) & ~15))[s];
+    }
   if constexpr (!NARROW_ONLY)
     if (map_lane) gmp = *reinterpret_cast<const uint4 *>((DIR == kFwd ? D.fgm : D.bgm) + gtr.x + 16 * s);
   int up = -1;  // kWrap: the layer's entry in D.parent, which names its row's bound term
@@ -399,7 +405,7 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
     wait();
     if (active) ly.begin_pass(D);
   }
-  // the maps into the stage (free until the staging below; the width scan's barriers publish them)
+  // the maps into the stage (free until the staging below; the barrier after the layers' records publishes them)
   if constexpr (!NARROW_ONLY)
     if (map_lane) reinterpret_cast<uint4 *>(s_cb)[s] = gmp;
 
@@ -416,40 +422,48 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
   uint32_t pkc[NARROW_ONLY ? 1 : kFlatR];
   if constexpr (!NARROW_ONLY) {
     GenTile &T = s_g;
-    // compact index of the tile's general layers (ballot prefix per wavefront), and exclusive
-    // prefix sums of their own and child widths (scan over the tile in position order)
+    // the general layers' ranks and the exclusive prefix sums of their own and child widths: from the
+    // tile's maps on the flat path (a scan here took 12 lane moves and two barriers of a tile's 6 us),
+    // by ballots and a scan over the tile in position order elsewhere
     gen = active && !ly.narrow();
-    const uint64_t mask = __ballot(gen);
     const int lane = s & 63, wv = s >> 6;
     const int w = gen ? (grec.z & 0xFFFF) : 0, wc = gen ? int(unsigned(grec.z) >> 16) : 0;
-    int iw = w, ic = wc;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int tw = __shfl_up(iw, o, 64), tc = __shfl_up(ic, o, 64);
-      if (lane >= o) {
-        iw += tw;
-        ic += tc;
+    int wo = int((gword >> kMapOwnShift) & kMapOwnMask), co = int(gword >> kMapChildShift);
+    if (flat) {
+      myk = int(gword & 0xFFu);
+      TW = gtr.y & 0xFFFF;
+      TC = int(uint32_t(gtr.y) >> 16);
+    } else {
+      const uint64_t mask = __ballot(gen);
+      int iw = w, ic = wc;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int tw = __shfl_up(iw, o, 64), tc = __shfl_up(ic, o, 64);
+        if (lane >= o) {
+          iw += tw;
+          ic += tc;
+        }
       }
-    }
-    if (lane == 63) {
-      s_wcnt[wv] = __popcll(mask);
-      s_d[wv] = __int_as_float(iw);
-      s_share[wv] = __int_as_float(ic);
-    }
-    __syncthreads();
-    int koff = 0, woff = 0, coff = 0;
-    for (int q = 0; q < kTile / 64; ++q) {
-      if (q < wv) {
-        koff += s_wcnt[q];
-        woff += __float_as_int(s_d[q]);
-        coff += __float_as_int(s_share[q]);
+      if (lane == 63) {
+        s_wcnt[wv] = __popcll(mask);
+        s_d[wv] = __int_as_float(iw);
+        s_share[wv] = __int_as_float(ic);
       }
-      ngen += s_wcnt[q];
-      TW += __float_as_int(s_d[q]);
-      TC += __float_as_int(s_share[q]);
-    }
-    __syncthreads();
-    if (gen) {
+      __syncthreads();
+      int koff = 0;
+      wo = iw - w;
+      co = ic - wc;
+      for (int q = 0; q < kTile / 64; ++q) {
+        if (q < wv) {
+          koff += s_wcnt[q];
+          wo += __float_as_int(s_d[q]);
+          co += __float_as_int(s_share[q]);
+        }
+        ngen += s_wcnt[q];
+      }
+      __syncthreads();
       myk = koff + __popcll(mask & ((1ull << lane) - 1ull));
+    }
+    if (gen) {
       T.os[myk] = grec.x;
       T.cs[myk] = grec.y;
       T.ww[myk] = grec.z;
@@ -459,8 +473,8 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
       } else {
         T.pcs[myk] = gnb.y;
       }
-      T.wo[myk] = woff + iw - w;
-      T.co[myk] = coff + ic - wc;
+      T.wo[myk] = wo;
+      T.co[myk] = co;
       T.lam[myk] = ly.lam0;
       T.m0[myk] = T.m1[myk] = ord_of(INFINITY);
     }

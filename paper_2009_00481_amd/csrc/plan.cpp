@@ -461,7 +461,7 @@ std::string validate_layout(const Plan &P, const std::vector<int32_t> &ownw, con
           if (off != -1) return "node map of a tile outside the flat stage";
           continue;
         }
-        const size_t len = (own.size() + chl.size() + 15) / 16 * 16;
+        const size_t map = (own.size() + chl.size() + 15) / 16 * 16, len = map + (4 * size_t(p1 - p0) + 15) / 16 * 16;
         if (off < 0 || off % 16 || size_t(off) != used || sizes != int32_t(own.size() | (chl.size() << 16)) ||
             size_t(off) + len > gm.size())
           return "node map record";
@@ -469,6 +469,16 @@ std::string validate_layout(const Plan &P, const std::vector<int32_t> &ownw, con
           if (gm[size_t(off) + q] != own[q]) return "own node map";
         for (size_t q = 0; q < chl.size(); ++q)
           if (gm[size_t(off) + own.size() + q] != chl[q]) return "child node map";
+        uint32_t r = 0, wo = 0, co = 0;
+        for (int64_t q = p0; q < p1; ++q) {
+          const int64_t L = (pass && wr.list) ? P.bwd_list[size_t(q)] : q;
+          if (((P.meta[size_t(L)] >> kMetaWidthShift) & 3u) != 0u) continue;
+          uint32_t x = 0;
+          for (int b = 0; b < 4; ++b) x |= uint32_t(gm[size_t(off) + map + 4 * size_t(q - p0) + size_t(b)]) << (8 * b);
+          if ((x & 0xFFu) != r++ || ((x >> kMapOwnShift) & kMapOwnMask) != wo || (x >> kMapChildShift) != co) return "layer map";
+          wo += uint32_t(ownw[size_t(L)]);
+          co += uint32_t(childw[size_t(L)]);
+        }
         used += len;
       }
     if (used != gm.size()) return "node map size";
@@ -1225,6 +1235,19 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
         for (int part = 0; part < 2; ++part)
           for (size_t k = 0; k < gen.size(); ++k)
             gm.insert(gm.end(), size_t(part ? childw[size_t(gen[k])] : ownw[size_t(gen[k])]), uint8_t(k));
+        gm.resize((gm.size() + 15) / 16 * 16, 0);
+        // then a word per position
+        uint32_t k = 0, wo = 0, co = 0;
+        for (int64_t q = p0; q < p1; ++q) {
+          const int64_t Lq = (pass && wr.list) ? P.bwd_list[size_t(q)] : q;
+          uint32_t x = 0;
+          if (((P.meta[size_t(Lq)] >> kMetaWidthShift) & 3u) == 0u) {
+            x = k++ | wo << kMapOwnShift | co << kMapChildShift;
+            wo += uint32_t(ownw[size_t(Lq)]);
+            co += uint32_t(childw[size_t(Lq)]);
+          }
+          for (int b = 0; b < 32; b += 8) gm.push_back(uint8_t(x >> b));
+        }
         gm.resize((gm.size() + 15) / 16 * 16, 0);
       }
     if (gm.size() >= size_t(INT32_MAX)) return set_error(BDDMP_BDD_TOO_LARGE, "node maps beyond 2^31 bytes");

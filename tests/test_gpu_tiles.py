@@ -1,6 +1,7 @@
 """GPU tests of the wave kernels' tiles at the edges of their forms, bitwise against the oracle's float
 mirror: the exchange sum of variables in few to many rows (blocks of eight and four rows, a workgroup's
-tile and more), rows that force the variable among them."""
+tile and more), rows that force the variable among them, and tiles of general levels at the sizes where
+their node maps end."""
 import numpy as np
 import pytest
 
@@ -38,3 +39,14 @@ def test_exchange_sums_bitwise(m, forced):
         rows.insert(int(rng.integers(0, len(rows) + 1)), (np.array([0]), np.array([1]), 1, 0))
     n = 1 + 2 * m
     _check(I.from_rows(n, rng.standard_normal(n, dtype=np.float32).astype(np.float64), rows), 3)
+
+
+@pytest.mark.parametrize("m,k,cmax,rhs", [(255, 5, 3, 7), (256, 5, 3, 7), (257, 5, 3, 7), (600, 4, 2, 4), (40, 9, 40, 120),
+                                          (9, 14, 300, 1500), (1, 12, 5, 20)])
+@pytest.mark.parametrize("work", [0, 2048, 100000])
+def test_general_tiles_bitwise(m, k, cmax, rhs, work):
+    """m rows over variables of their own: every wave holds one level of each row."""
+    rng = np.random.default_rng([m, k, cmax])
+    rows = [(np.arange(j * k, (j + 1) * k), rng.integers(1, cmax + 1, k), 1, rhs) for j in range(m)]
+    n = m * k
+    _check(I.from_rows(n, rng.standard_normal(n, dtype=np.float32).astype(np.float64), rows), 2, tile_work=work)
