@@ -66,11 +66,12 @@ __device__ __forceinline__ float updated(float lam0, float d, float share, int n
   return nf == 0 ? (lam0 - d) + share : (isinf(d) ? lam0 + share : lam0 - d);
 }
 
-// Sum and number of forced rows of a variable's differences d[0 .. len), in ascending row order. The
-// loads of up to eight rows are issued together and only the additions run in sequence (one load per
-// addition takes an LDS round trip, about 100 cycles, per row: half a wave's time on graph matching,
-// where variables have up to about 45 rows). A sum that is not finite is taken again with the infinite
-// differences apart.
+// Sum and number of forced rows of a variable's differences d[0 .. len), in ascending row order, infinite
+// differences apart. The loads of up to eight rows are issued together and only the additions run in
+// sequence (one load per addition takes an LDS round trip, about 100 cycles, per row: half a wave's time
+// on graph matching, where variables have up to about 45 rows). Blocks of eight are summed as if all were
+// finite, and again in blocks of four, which count the infinite ones, if the sum is not. (No loop is
+// unrolled further: in a launch of a few microseconds the fetch of code counts.)
 struct RowSum {
   float sum;
   int nf;
@@ -78,6 +79,7 @@ struct RowSum {
 __device__ __forceinline__ RowSum row_sum(const float *d, int len) {
   RowSum r{0.0f, 0};
   int q = 0;
+#pragma unroll 1
   for (; q + 8 <= len; q += 8) {
     float x[8];
 #pragma unroll
@@ -85,19 +87,21 @@ __device__ __forceinline__ RowSum row_sum(const float *d, int len) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) r.sum += x[t];
   }
+  if (!isfinite(r.sum)) {
+    r.sum = 0.0f;
+    q = 0;
+  }
+#pragma unroll 1
   for (; q < len; q += 4) {
     float x[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) x[t] = d[min(q + t, len - 1)];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) r.sum = q + t < len ? r.sum + x[t] : r.sum;
-  }
-  if (isfinite(r.sum)) return r;
-  r.sum = 0.0f;
-  for (q = 0; q < len; ++q) {
-    const float x = d[q];
-    if (isinf(x)) ++r.nf;
-    else r.sum += x;
+    for (int t = 0; t < 4; ++t) {
+      const bool in = q + t < len, apart = in && isinf(x[t]);
+      r.sum = in && !apart ? r.sum + x[t] : r.sum;
+      r.nf += apart;
+    }
   }
   return r;
 }

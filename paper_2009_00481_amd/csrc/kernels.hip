@@ -307,13 +307,10 @@ __device__ __forceinline__ float staged(const float *cb, int c0, uint32_t c) {
 template <bool NARROW_ONLY>
 struct WaveLds {
   float d[kTile];
-  int wcnt[kTile / 64];
+  float d2[NARROW_ONLY ? kTile : 1];  // differences of a fused wave's second round
+  int wcnt[3][kTile / 64];
   // general-layer paths (one element in narrow-only instantiations)
   std::conditional_t<NARROW_ONLY, int, GenTile> g;
-  // J_i shares and forced-row counts; with general layers they reuse the min-marginal words, which
-  // are read before the update begins (fewer LDS bytes per workgroup, more workgroups per CU)
-  float share_n[NARROW_ONLY ? kTile : 1];
-  int nf_n[NARROW_ONLY ? kTile : 1];
   // flat path: first the tile's node maps, then the next levels' backward messages; in a forward
   // tile, once the min-marginals are taken, the own levels' forward messages for the pull (one
   // array serves all three, so that more workgroups fit a CU's LDS)
@@ -343,18 +340,7 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
   // messages this pass writes
   constexpr bool kDeferred = !std::is_same_v<Wait, NoWait>;
   static_assert(!kDeferred || MODE == kUpdate, "deferred waits: update mode");
-  float *const s_d = sh.d;
-  int *const s_wcnt = sh.wcnt;
   auto &s_g = sh.g;
-  float *s_share;
-  int *s_nf;
-  if constexpr (NARROW_ONLY) {
-    s_share = sh.share_n;
-    s_nf = sh.nf_n;
-  } else {
-    s_share = reinterpret_cast<float *>(s_g.m0);
-    s_nf = reinterpret_cast<int *>(s_g.m1);
-  }
   float *const s_cb = sh.cb;
   float *const s_fu = s_cb;
   const int p0 = int(w0 & kTilePosMask);
@@ -444,9 +430,9 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
         }
       }
       if (lane == 63) {
-        s_wcnt[wv] = __popcll(mask);
-        s_d[wv] = __int_as_float(iw);
-        s_share[wv] = __int_as_float(ic);
+        sh.wcnt[0][wv] = __popcll(mask);
+        sh.wcnt[1][wv] = iw;
+        sh.wcnt[2][wv] = ic;
       }
       __syncthreads();
       int koff = 0;
@@ -454,13 +440,12 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
       co = ic - wc;
       for (int q = 0; q < kTile / 64; ++q) {
         if (q < wv) {
-          koff += s_wcnt[q];
-          wo += __float_as_int(s_d[q]);
-          co += __float_as_int(s_share[q]);
+          koff += sh.wcnt[0][q];
+          wo += sh.wcnt[1][q];
+          co += sh.wcnt[2][q];
         }
-        ngen += s_wcnt[q];
+        ngen += sh.wcnt[0][q];
       }
-      __syncthreads();
       myk = koff + __popcll(mask & ((1ull << lane) - 1ull));
     }
     if (gen) {
@@ -494,49 +479,67 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
       // array, and is marked unused): with a branch per slot the compiler waited for one slot's
       // loads before issuing the next slot's.
       const uint8_t *maps = reinterpret_cast<const uint8_t *>(s_cb);
-      int ks[kFlatR], kcs[kFlatR];
-#pragma unroll
-      for (int r = 0; r < kFlatR; ++r) {
-        const int t = s + r * kTile;
-        ks[r] = t < TW ? int(maps[t]) : 0;
-        kcs[r] = t < TC ? int(maps[TW + t]) : 0;
-      }
-#pragma unroll
-      for (int r = 0; r < kFlatR; ++r) {
-        const int t = s + r * kTile;
-        const bool ok = r * kTile < TW && t < TW;
-        const int k = ks[r];
-        const int u = ok ? t - T.wo[k] : 0;
-        const int q = ok ? T.os[k] + u : 2 * p0;
-        kr[r] = ok ? k : -1;
-        ur[r] = u;
-        ar[r] = D.garcs[q];
-        fr[r] = msg_ld<COH && DIR == kFwd>(D.mf + q);
-      }
-      // all loads of the lane first, then the LDS stores: a store right after its load would wait
-      // for that load before the next one issues
+      const int nodes = max(TW, TC);
       float cbr[kFlatR];
 #pragma unroll
       for (int r = 0; r < kFlatR; ++r) {
-        const int t = s + r * kTile;
-        const bool ok = r * kTile < TC && t < TC;
-        const int k = kcs[r];
-        kc[r] = ok ? k : -1;
-        cbr[r] = msg_ld<COH && DIR == kBwd>(D.mbc + (ok ? T.cs[k] + (t - T.co[k]) : 2 * p0));
-      }
-      // the packed in-arcs (no slot of that array exists in every plan, so these stay conditional
-      // and go last)
-#pragma unroll
-      for (int r = 0; r < kFlatR; ++r) {
+        kr[r] = kc[r] = -1;
+        ur[r] = 0;
+        ar[r] = 0u;
+        fr[r] = cbr[r] = 0.0f;
         pkc[r] = kManyInArcs;
-        const int k = kc[r];
-        if (DIR == kFwd && k >= 0 && T.osc[k] >= 0) pkc[r] = D.rin[T.rb[k] + (s + r * kTile - T.co[k])];
+      }
+      // two slots at a time as far as the tile's nodes go (one branch, the same for every lane): most
+      // tiles of a wave that leaves the GPU free have at most kTileFewWork nodes
+#pragma unroll
+      for (int r0 = 0; r0 < kFlatR; r0 += 2) {
+        if (r0 * kTile >= nodes) break;
+        int ks[2], kcs[2];
+#pragma unroll
+        for (int r = r0; r < r0 + 2; ++r) {
+          const int t = s + r * kTile;
+          ks[r - r0] = t < TW ? int(maps[t]) : 0;
+          kcs[r - r0] = t < TC ? int(maps[TW + t]) : 0;
+        }
+#pragma unroll
+        for (int r = r0; r < r0 + 2; ++r) {
+          const int t = s + r * kTile;
+          const bool ok = t < TW;
+          const int k = ks[r - r0];
+          const int u = ok ? t - T.wo[k] : 0;
+          const int q = ok ? T.os[k] + u : 2 * p0;
+          kr[r] = ok ? k : -1;
+          ur[r] = u;
+          ar[r] = D.garcs[q];
+          fr[r] = msg_ld<COH && DIR == kFwd>(D.mf + q);
+        }
+        // all loads of the lane first, then the LDS stores: a store right after its load would wait
+        // for that load before the next one issues
+#pragma unroll
+        for (int r = r0; r < r0 + 2; ++r) {
+          const int t = s + r * kTile;
+          const bool ok = t < TC;
+          const int k = kcs[r - r0];
+          kc[r] = ok ? k : -1;
+          cbr[r] = msg_ld<COH && DIR == kBwd>(D.mbc + (ok ? T.cs[k] + (t - T.co[k]) : 2 * p0));
+        }
+        // the packed in-arcs (no slot of that array exists in every plan, so these stay conditional
+        // and go last)
+        if constexpr (DIR == kFwd) {
+#pragma unroll
+          for (int r = r0; r < r0 + 2; ++r) {
+            const int k = kc[r];
+            if (k >= 0 && T.osc[k] >= 0) pkc[r] = D.rin[T.rb[k] + (s + r * kTile - T.co[k])];
+          }
+        }
       }
       // every lane has read its ranks before the stage takes the backward messages
       __syncthreads();
 #pragma unroll
-      for (int r = 0; r < kFlatR; ++r)
+      for (int r = 0; r < kFlatR; ++r) {
+        if (r * kTile >= nodes) break;
         if (kc[r] >= 0) s_cb[s + r * kTile] = cbr[r];
+      }
       __syncthreads();
 #pragma unroll
       for (int r = 0; r < kFlatR; ++r) {
@@ -581,8 +584,10 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
       if (active && !gen) ly.take_pass(pass_pair);
     if (DIR == kFwd && flat) {
 #pragma unroll
-      for (int r = 0; r < kFlatR; ++r)
+      for (int r = 0; r < kFlatR; ++r) {
+        if (r * kTile >= TW) break;
         if (kr[r] >= 0) s_fu[s + r * kTile] = fr[r];
+      }
       // the pull below reads them after the barrier that publishes the new multipliers
     }
   }
@@ -606,19 +611,15 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
         ly.narrow_marginals(lam1);
         d = ly.m1 - ly.m0;
       }
-      // the previous round's readers of s_d and s_share are past the barriers that follow
+      float *const s_d = round ? sh.d2 : sh.d;
       s_d[s] = d;
       __syncthreads();
-      if (active && pos == 0) {
-        // J_i sum in ascending row order (the segment is sorted by row)
-        const RowSum r = row_sum(s_d + s, len);
-        s_share[s] = r.sum / float(r.nf ? r.nf : len);
-        s_nf[s] = r.nf;
-      }
-      __syncthreads();
       if (active) {
-        const int h = s - pos;
-        lam1 = updated(lam1, d, s_share[h], s_nf[h]);
+        // J_i sum in ascending row order (the segment is sorted by row), by every lane of the segment
+        // for itself: a wavefront takes the same time as for one lane, and the result need not be
+        // handed on through LDS and a barrier
+        const RowSum r = row_sum(s_d + (s - pos), len);
+        lam1 = updated(lam1, d, r.sum / float(r.nf ? r.nf : len), r.nf);
       }
       if constexpr (MODE == kWrap) {
         // the backward step at the roots with the updated multipliers: E^j of each row
@@ -643,6 +644,7 @@ __device__ __forceinline__ void wave_tile(const Dev &D, WaveLds<NARROW_ONLY> &sh
         // "Forward BDD update step"), reading this level's forward messages from LDS
 #pragma unroll
         for (int r = 0; r < kFlatR; ++r) {
+          if (r * kTile >= TC) break;
           const int k = kc[r];
           if (k >= 0) {
             const int osc = T.osc[k];
@@ -918,8 +920,7 @@ template <int DIR>
 __global__ __launch_bounds__(kTile) __attribute__((amdgpu_waves_per_eu(8)))
 void group_pair_kernel(const Dev D, const GroupArgs A) {
   __shared__ WaveLds<true> sh;
-  __shared__ float p_d[2][kTile], p_share[2][kTile];
-  __shared__ int p_nf[2][kTile];
+  __shared__ float p_d[2][kTile];
   const int s = int(threadIdx.x);
   const int ta = A.t0 + 2 * int(blockIdx.x);
   const bool two = ta + 1 < A.t_end;
@@ -991,19 +992,11 @@ void group_pair_kernel(const Dev D, const GroupArgs A) {
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < 2; ++k)
-    if (act[k] && pos[k] == 0) {
-      // J_i sum in ascending row order (the segment is sorted by row)
-      const RowSum r = row_sum(&p_d[k][s], len[k]);
-      p_share[k][s] = r.sum / float(r.nf ? r.nf : len[k]);
-      p_nf[k][s] = r.nf;
-    }
-  __syncthreads();
-#pragma unroll
   for (int k = 0; k < 2; ++k) {
     if (act[k]) {
-      const int h = s - pos[k];
-      lam1[k] = updated(lam1[k], d[k], p_share[k][h], p_nf[k][h]);
+      // J_i sum in ascending row order (the segment is sorted by row), by each of its lanes
+      const RowSum r = row_sum(&p_d[k][s - pos[k]], len[k]);
+      lam1[k] = updated(lam1[k], d[k], r.sum / float(r.nf ? r.nf : len[k]), r.nf);
       D.lam[ly[k].L] = lam1[k];
     }
     if (act[k]) {
