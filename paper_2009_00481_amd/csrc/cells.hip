@@ -98,20 +98,6 @@ __device__ __forceinline__ float2 regular_bstep(bool c, float2 b, float lam) {
   return c ? make_float2(v, b.y) : make_float2(b.x, v);
 }
 
-// any narrow level, by its 2-bit child codes
-__device__ __forceinline__ float2 narrow_push(uint32_t a, float2 f, float lam) {
-  const uint32_t k0 = a & 3u, k1 = (a >> 2) & 3u, k2 = (a >> 4) & 3u, k3 = (a >> 6) & 3u;
-  const float a0 = f.x, a1 = f.x + lam, a2 = f.y, a3 = f.y + lam;
-  return make_float2(fminf(fminf(k0 == 0u ? a0 : INFINITY, k1 == 0u ? a1 : INFINITY),
-                           fminf(k2 == 0u ? a2 : INFINITY, k3 == 0u ? a3 : INFINITY)),
-                     fminf(fminf(k0 == 1u ? a0 : INFINITY, k1 == 1u ? a1 : INFINITY),
-                           fminf(k2 == 1u ? a2 : INFINITY, k3 == 1u ? a3 : INFINITY)));
-}
-__device__ __forceinline__ float2 narrow_bstep(uint32_t a, float2 b, float lam) {
-  return make_float2(fminf(c2val(a & 3u, b), c2val((a >> 2) & 3u, b) + lam),
-                     fminf(c2val((a >> 4) & 3u, b), c2val((a >> 6) & 3u, b) + lam));
-}
-
 // Levels of up to four nodes (kCellGen). Each arc names the float of X behind it: its child's on the
 // layer's own link, or one of the constants 0 (TOP) and +inf (BOT, and the arcs of absent nodes), so a
 // node costs two LDS reads and no decoding. w: nodes of the level, or of the widest in the chunk.

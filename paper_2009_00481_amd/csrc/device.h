@@ -109,6 +109,52 @@ __device__ __forceinline__ RowSum row_sum(const float *d, int len) {
 // Bound term index of a root layer from its entry in D.parent.
 __device__ __forceinline__ int root_term(int up) { return kRootTerm0 - up; }
 
+// any narrow level, by its 2-bit child codes
+__device__ __forceinline__ float2 narrow_push(uint32_t a, float2 f, float lam) {
+  const uint32_t k0 = a & 3u, k1 = (a >> 2) & 3u, k2 = (a >> 4) & 3u, k3 = (a >> 6) & 3u;
+  const float a0 = f.x, a1 = f.x + lam, a2 = f.y, a3 = f.y + lam;
+  return make_float2(fminf(fminf(k0 == 0u ? a0 : INFINITY, k1 == 0u ? a1 : INFINITY),
+                           fminf(k2 == 0u ? a2 : INFINITY, k3 == 0u ? a3 : INFINITY)),
+                     fminf(fminf(k0 == 1u ? a0 : INFINITY, k1 == 1u ? a1 : INFINITY),
+                           fminf(k2 == 1u ? a2 : INFINITY, k3 == 1u ? a3 : INFINITY)));
+}
+__device__ __forceinline__ float2 narrow_bstep(uint32_t a, float2 b, float lam) {
+  return make_float2(fminf(c2val(a & 3u, b), c2val((a >> 2) & 3u, b) + lam),
+                     fminf(c2val((a >> 4) & 3u, b), c2val((a >> 6) & 3u, b) + lam));
+}
+
+// A row's backward messages under the current multipliers, by one lane from the row's last level to its
+// root: rows are independent, so no wave has to wait for another, and the row's layers (contiguous in
+// layer_of) are read eight levels at a time, their loads in flight together. step(meta, b, lam): the
+// level's message from its child level's. All levels of the row are narrow.
+template <class Step>
+__device__ __forceinline__ void row_sweep(const Dev &D, int j, Step step) {
+  constexpr int Q = 8;
+  const int c0 = D.bdd_canon_off[j], k = D.bdd_canon_off[j + 1] - c0;
+  if (k <= 0) return;
+  const int up = D.parent[D.layer_of[c0]];
+  float2 m = make_float2(INFINITY, INFINITY);  // a last level's arcs end in terminals
+  for (int e = k; e > 0; e -= Q) {
+    int L[Q + 1];
+#pragma unroll
+    for (int t = 0; t <= Q; ++t) L[t] = D.layer_of[c0 + max(e - 1 - t, 0)];
+    uint32_t meta[Q];
+    float lam[Q];
+#pragma unroll
+    for (int t = 0; t < Q; ++t) {
+      meta[t] = D.meta[L[t]];
+      lam[t] = D.lam[L[t]];
+    }
+#pragma unroll
+    for (int t = 0; t < Q; ++t) {
+      if (e - 1 - t < 0) break;
+      m = step(meta[t], m, lam[t]);
+      if (e - 1 - t > 0) reinterpret_cast<float2 *>(D.mbc)[L[t + 1]] = m;
+    }
+  }
+  if (up <= kRootTerm0) D.root_e[root_term(up)] = m.x;
+}
+
 // General record of a layer: own slot, child slot, own width, child width, base of the child
 // level's in-arc offsets (-1 without child level).
 struct GRec {

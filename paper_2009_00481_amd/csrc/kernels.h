@@ -73,6 +73,9 @@ struct Dev {
   const uint8_t *fgm, *bgm;
 };
 
+// Initial sweep (kBwd) or min-marginals to the outputs and messages (kFwd, as kExtract) of a plan of
+// narrow levels without cuts, one lane per row (m rows).
+hipError_t launch_rows(int dir, int m, const Dev &D, hipStream_t s);
 // One wave: nt normal tiles from tile0 of the pass's tile list (dir kFwd / kBwd, mode as above).
 // narrow_only selects the variant without wide levels, list the backward index-list variant.
 // kWrap: dir kFwd, narrow-only, no list.
@@ -173,6 +176,7 @@ hipError_t launch_copy_io(const Dev &D, int n_cuts, bool out, float *mu_bar, flo
 struct SmoothArgs {
   float alpha;
   float root_seed;        // adjoint of each root's new backward message in this pass
+  const float *lam_in;    // multipliers an update pass starts from (it leaves the new ones in D.lam)
   const float *lam_prev;  // multipliers before the pass's updates
   const float *lam_upd;   // multipliers after the forward pass's updates
   const float *mbt;       // backward messages the forward pass read
@@ -181,6 +185,8 @@ struct SmoothArgs {
 // One wave of a smoothed pass (adjoint = false) or of its adjoint (true).
 hipError_t launch_smooth_wave(int dir, int mode, bool adjoint, bool list, int nt, int tile0, const Dev &D,
                               const SmoothArgs &A, hipStream_t s);
+// The smoothed initial sweep of a plan of narrow levels, one lane per row (m rows).
+hipError_t launch_smooth_rows(int m, const Dev &D, float alpha, hipStream_t s);
 // D.lbc[0] = sum of min(0, c_i), D.lbc[1] = sum of smin_alpha(0, c_i) over variables in no row.
 hipError_t launch_free_const(const Dev &D, int n, float alpha, hipStream_t s);
 hipError_t launch_smooth_grad(const Dev &D, const SmoothArgs &A, int n, float scale, float *grad, hipStream_t s);

@@ -1057,6 +1057,49 @@ __global__ __launch_bounds__(kTile) void wave_big_kernel(const Dev D, const int 
   }
 }
 
+// Initial sweep and min-marginals of a plan of narrow levels, one lane per row.
+__global__ __launch_bounds__(kTile) void row_sweep_kernel(const Dev D, int m) {
+  const int j = int(blockIdx.x) * kTile + int(threadIdx.x);
+  if (j < m) row_sweep(D, j, [](uint32_t meta, float2 b, float lam) { return narrow_bstep(meta, b, lam); });
+}
+
+__global__ __launch_bounds__(kTile) void row_extract_kernel(const Dev D, int m) {
+  constexpr int Q = 8;
+  const int j = int(blockIdx.x) * kTile + int(threadIdx.x);
+  if (j >= m) return;
+  const int c0 = D.bdd_canon_off[j], k = D.bdd_canon_off[j + 1] - c0;
+  if (k <= 0) return;
+  float2 *mf = reinterpret_cast<float2 *>(D.mf);
+  const float2 *mbc = reinterpret_cast<const float2 *>(D.mbc);
+  float2 f = mf[D.layer_of[c0]];
+  for (int e = 0; e < k; e += Q) {
+    int L[Q + 1];
+#pragma unroll
+    for (int t = 0; t <= Q; ++t) L[t] = D.layer_of[c0 + min(e + t, k - 1)];
+    uint32_t meta[Q];
+    float lam[Q];
+    float2 b[Q];
+#pragma unroll
+    for (int t = 0; t < Q; ++t) {
+      meta[t] = D.meta[L[t]];
+      lam[t] = D.lam[L[t]];
+      b[t] = mbc[L[t]];
+    }
+#pragma unroll
+    for (int t = 0; t < Q; ++t) {
+      if (e + t >= k) break;
+      const uint32_t a = meta[t];
+      const float m0 = fminf(f.x + c2val(a & 3u, b[t]), f.y + c2val((a >> 4) & 3u, b[t]));
+      const float m1 = fminf((f.x + lam[t]) + c2val((a >> 2) & 3u, b[t]), (f.y + lam[t]) + c2val((a >> 6) & 3u, b[t]));
+      if (D.out0) D.out0[c0 + e + t] = m0;
+      if (D.out1) D.out1[c0 + e + t] = m1;
+      D.d_fresh[L[t]] = m1 - m0;
+      f = narrow_push(a, f, lam[t]);
+      if (e + t + 1 < k) mf[L[t + 1]] = f;
+    }
+  }
+}
+
 __global__ void fill_kernel(float *p, float v, int n) {
   const int i = int(blockIdx.x) * blockDim.x + int(threadIdx.x);
   if (i < n) p[i] = v;
@@ -1329,6 +1372,13 @@ static hipError_t wave_dispatch(bool narrow_only, bool list, int nt, int tile0, 
     hipLaunchKernelGGL((wave_kernel<DIR, MODE, false, false>), dim3(nt), dim3(kTile), 0, s, D, tile0);
   else
     hipLaunchKernelGGL((wave_kernel<DIR, MODE, false, true>), dim3(nt), dim3(kTile), 0, s, D, tile0);
+  return hipGetLastError();
+}
+
+hipError_t launch_rows(int dir, int m, const Dev &D, hipStream_t s) {
+  if (m <= 0) return hipSuccess;
+  if (dir == kBwd) hipLaunchKernelGGL(row_sweep_kernel, dim3(blocks_for(m, kTile)), dim3(kTile), 0, s, D, m);
+  else hipLaunchKernelGGL(row_extract_kernel, dim3(blocks_for(m, kTile)), dim3(kTile), 0, s, D, m);
   return hipGetLastError();
 }
 

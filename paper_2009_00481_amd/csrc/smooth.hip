@@ -91,42 +91,42 @@ struct Seg {
   bool neg;
 };
 
-// J_i sums of a tile's segments: the head lane of each variable reads its rows' differences in
-// ascending row order and leaves the share, the forced count and the forced sign for its lanes
-__device__ __forceinline__ Seg seg_update(float d, uint32_t meta, bool active, float *s_d, float *s_share, int *s_nf) {
+// J_i sums of a tile's segments: every lane reads its variable's differences in ascending row order, for
+// the share, the forced count and the forced sign
+__device__ __forceinline__ Seg seg_update(float d, uint32_t meta, bool active, float *s_d) {
   const int s = int(threadIdx.x);
   s_d[s] = d;
   __syncthreads();
-  const int pos = int((meta >> kMetaPosShift) & kMetaField);
+  Seg g{0.0f, 0, false};
+  if (!active) return g;
   const int len = int((meta >> kMetaLenShift) & kMetaField);
-  if (active && pos == 0) {
-    RowSum r = row_sum(s_d + s, len);
-    int neg = 0;
-    if (r.nf) {
-      for (int q = 0; q < len; ++q)
-        if (isinf(s_d[s + q]) && s_d[s + q] < 0.0f) neg = 1;
-      r.sum = 0.0f;
-      for (int q = 0; q < len; ++q)
-        if (moving(s_d[s + q], neg)) r.sum += s_d[s + q];
-    }
-    s_share[s] = r.sum / float(r.nf ? r.nf : len);
-    s_nf[s] = r.nf | (neg << 30);
+  const float *v = s_d + (s - int((meta >> kMetaPosShift) & kMetaField));
+  RowSum r = row_sum(v, len);
+  if (r.nf) {
+    for (int q = 0; q < len; ++q)
+      if (isinf(v[q]) && v[q] < 0.0f) g.neg = true;
+    r.sum = 0.0f;
+    for (int q = 0; q < len; ++q)
+      if (moving(v[q], g.neg)) r.sum += v[q];
   }
-  __syncthreads();
-  const int h = s - pos;
-  Seg r;
-  r.share = s_share[h];
-  r.nf = s_nf[h] & ~(1 << 30);
-  r.neg = (s_nf[h] >> 30) & 1;
-  return r;
+  g.share = r.sum / float(r.nf ? r.nf : len);
+  g.nf = r.nf;
+  return g;
+}
+
+__global__ __launch_bounds__(kTile) void smooth_rows_kernel(const Dev D, int m, float alpha) {
+  const int j = int(blockIdx.x) * kTile + int(threadIdx.x);
+  if (j < m)
+    row_sweep(D, j, [=](uint32_t meta, float2 b, float lam) {
+      return make_float2(smin(c2val(meta & 3u, b), c2val((meta >> 2) & 3u, b) + lam, alpha),
+                         smin(c2val((meta >> 4) & 3u, b), c2val((meta >> 6) & 3u, b) + lam, alpha));
+    });
 }
 
 // Smoothed forward (DIR kFwd) or backward (kBwd) wave; MODE kUpdate or kNoUpdate (initial sweep).
 template <int DIR, int MODE, bool LIST>
 __global__ __launch_bounds__(kTile) void smooth_wave_kernel(const Dev D, const SmoothArgs A, const int tile0) {
   __shared__ float s_d[kTile];
-  __shared__ float s_share[kTile];
-  __shared__ int s_nf[kTile];
   const int32_t *tiles = DIR == kFwd ? D.fwd_tiles : D.bwd_tiles;
   const int tix = tile0 + xcd_tile(int(blockIdx.x), int(gridDim.x));
   const int p0 = int(uint32_t(tiles[2 * tix]) & kTilePosMask);
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kTile) void smooth_wave_kernel(const Dev D, const S
   if (active) {
     L = (DIR == kBwd && LIST) ? D.bwd_list[p0 + s] : p0 + s;
     meta = D.meta[L];
-    lam0 = D.lam[L];
+    lam0 = MODE == kUpdate ? A.lam_in[L] : D.lam[L];
     tgt = DIR == kFwd ? D.child[L] : D.parent[L];
     f = reinterpret_cast<const float2 *>(D.mf)[L];
     b = reinterpret_cast<const float2 *>(D.mbc)[L];
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kTile) void smooth_wave_kernel(const Dev D, const S
     SMarg m{0.0f, 0.0f};
     if (active) m = narrow ? s_marg_narrow(meta, f, b, lam0, alpha) : s_marg_general(D, grec_of(D, L), D.mbc, lam0, alpha);
     const float d = m.m1 - m.m0;
-    const Seg g = seg_update(d, meta, active, s_d, s_share, s_nf);
+    const Seg g = seg_update(d, meta, active, s_d);
     if (active) {
       lam1 = s_updated(lam0, d, g.share, g.nf, g.neg);
       D.lam[L] = lam1;
@@ -201,34 +201,34 @@ __global__ __launch_bounds__(kTile) void smooth_wave_kernel(const Dev D, const S
 
 // Adjoint of the J_i update: given the adjoints of the updated multipliers (gl1), the adjoints of
 // the differences. Forced rows: no derivative through their infinite difference.
-__device__ __forceinline__ float seg_adjoint(float d, float gl1, uint32_t meta, bool active, float *s_d, float *s_g,
-                                             float *s_a, int *s_nf) {
+__device__ __forceinline__ float seg_adjoint(float d, float gl1, uint32_t meta, bool active, float *s_d, float *s_g) {
   const int s = int(threadIdx.x);
   s_d[s] = d;
   s_g[s] = gl1;
   __syncthreads();
-  const int pos = int((meta >> kMetaPosShift) & kMetaField);
-  const int len = int((meta >> kMetaLenShift) & kMetaField);
-  if (active && pos == 0) {
-    float gsum = 0.0f, gforced = 0.0f;
-    int nf = 0, neg = 0;
-    for (int q = 0; q < len; ++q) {
-      const float dq = s_d[s + q];
-      if (isinf(dq)) {
-        ++nf;
-        gforced += s_g[s + q];
-        if (dq < 0.0f) neg = 1;
-      }
-      gsum += s_g[s + q];
+  if (!active) return 0.0f;
+  const int len = int((meta >> kMetaLenShift) & kMetaField), h = s - int((meta >> kMetaPosShift) & kMetaField);
+  float gsum = 0.0f, gforced = 0.0f;
+  int nf = 0;
+  bool neg = false;
+#pragma unroll 1
+  for (int q = 0; q < len; q += 4) {
+    float x[4], y[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      x[t] = s_d[h + min(q + t, len - 1)];
+      y[t] = s_g[h + min(q + t, len - 1)];
     }
-    s_a[s] = nf ? gforced / float(nf) : gsum / float(len);
-    s_nf[s] = nf | (neg << 30);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const bool in = q + t < len, forced = in && isinf(x[t]);
+      gsum = in ? gsum + y[t] : gsum;
+      gforced = forced ? gforced + y[t] : gforced;
+      nf += forced;
+      neg = neg || (forced && x[t] < 0.0f);
+    }
   }
-  __syncthreads();
-  const int h = s - pos;
-  const float avg = s_a[h];
-  const int nf = s_nf[h] & ~(1 << 30);
-  const bool neg = (s_nf[h] >> 30) & 1;
+  const float avg = nf ? gforced / float(nf) : gsum / float(len);
   if (nf == 0) return -gl1 + avg;
   return moving(d, neg) ? -gl1 + avg : 0.0f;
 }
@@ -244,8 +244,6 @@ template <int DIR, int MODE, bool LIST>
 __global__ __launch_bounds__(kTile) void smooth_adjoint_kernel(const Dev D, const SmoothArgs A, const int tile0) {
   __shared__ float s_d[kTile];
   __shared__ float s_g[kTile];
-  __shared__ float s_a[kTile];
-  __shared__ int s_nf[kTile];
   const int32_t *tiles = DIR == kFwd ? D.fwd_tiles : D.bwd_tiles;
   const int tix = tile0 + xcd_tile(int(blockIdx.x), int(gridDim.x));
   const int p0 = int(uint32_t(tiles[2 * tix]) & kTilePosMask);
@@ -378,7 +376,7 @@ __global__ __launch_bounds__(kTile) void smooth_adjoint_kernel(const Dev D, cons
     SMarg m{0.0f, 0.0f};
     if (active) m = narrow ? s_marg_narrow(meta, f, b, lam0, alpha) : s_marg_general(D, g, mbr, lam0, alpha);
     const float d = m.m1 - m.m0;
-    const float gd = seg_adjoint(d, gl, meta, active, s_d, s_g, s_a, s_nf);
+    const float gd = seg_adjoint(d, gl, meta, active, s_d, s_g);
     // phase 3: the min-marginals
     if (active && !isinf(d) && gd != 0.0f) {
       if (narrow) {
@@ -510,6 +508,12 @@ hipError_t launch_smooth_wave(int dir, int mode, bool adjoint, bool list, int nt
   if (dir == kBwd && mode == kUpdate) return smooth_dispatch<kBwd, kUpdate>(adjoint, list, nt, tile0, D, A, s);
   if (dir == kBwd && mode == kNoUpdate) return smooth_dispatch<kBwd, kNoUpdate>(adjoint, list, nt, tile0, D, A, s);
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_smooth_rows(int m, const Dev &D, float alpha, hipStream_t s) {
+  if (m <= 0) return hipSuccess;
+  hipLaunchKernelGGL(smooth_rows_kernel, dim3(blocks_of(m, kTile)), dim3(kTile), 0, s, D, m, alpha);
+  return hipGetLastError();
 }
 
 hipError_t launch_free_const(const Dev &D, int n, float alpha, hipStream_t s) {

@@ -1,7 +1,7 @@
 """GPU tests of the wave kernels' tiles at the edges of their forms, bitwise against the oracle's float
 mirror: the exchange sum of variables in few to many rows (blocks of eight and four rows, a workgroup's
-tile and more), rows that force the variable among them, and tiles of general levels at the sizes where
-their node maps end."""
+tile and more), rows that force the variable among them, tiles of general levels at the sizes where
+their node maps end, and the passes that run by rows."""
 import numpy as np
 import pytest
 
@@ -50,3 +50,34 @@ def test_general_tiles_bitwise(m, k, cmax, rhs, work):
     rows = [(np.arange(j * k, (j + 1) * k), rng.integers(1, cmax + 1, k), 1, rhs) for j in range(m)]
     n = m * k
     _check(I.from_rows(n, rng.standard_normal(n, dtype=np.float32).astype(np.float64), rows), 2, tile_work=work)
+
+
+@pytest.mark.parametrize("k", [1, 2, 7, 8, 9, 15, 16, 17, 40])
+@pytest.mark.parametrize("m", [1, 255, 257])
+def test_row_passes_bitwise(m, k):
+    """Initial sweep from given multipliers and min-marginals by rows, at the edges of their blocks of eight
+    levels and of a workgroup's rows; m rows of k to k + 2 levels, each sharing a variable with the next."""
+    rng = np.random.default_rng([m, k])
+    rows, v = [], 0
+    for j in range(m):
+        kk = k + j % 3 if k > 1 else 1
+        rows.append((np.arange(v, v + kk), np.ones(kk, int), j % 2, 1))
+        v += max(kk - 1, 1)
+    n = v + 2
+    ilp = I.from_rows(n, rng.standard_normal(n, dtype=np.float32).astype(np.float64), rows)
+    plan = B.Plan(B.Problem.from_ilp(ilp))
+    lam = rng.standard_normal(int(plan.stats.n_incidences)).astype(np.float32)
+    import torch
+
+    s = B.Solver(plan)
+    s.set_lambda(torch.from_numpy(lam).cuda())
+    o = Oracle(I.ILP(ilp.n, ilp.cost, ilp.row_ptr, ilp.col, ilp.coef, ilp.sense, ilp.rhs, plan.order()), precision="f32")
+    o.init()
+    o.set_lambda(lam.astype(np.float64))
+    for step in range(2):
+        m0, m1 = s.min_marginals()
+        r0, r1 = o.min_marginals()
+        assert np.array_equal(m0.cpu().numpy().astype(np.float64), r0) and np.array_equal(m1.cpu().numpy().astype(np.float64), r1)
+        np.testing.assert_allclose(s.lb_history(1)[-1], o.lower_bound(), rtol=1e-12, atol=1e-9)
+        s.iterate(1)
+        o.iterate(1)
