@@ -670,6 +670,7 @@ bool build_cells(Plan &P, const std::vector<int64_t> &iptr, const std::vector<in
 // row's previous level. Empty when sound.
 std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, const std::vector<int32_t> &childw) {
   std::vector<uint8_t> seen(size_t(P.I), 0);
+  std::vector<int32_t> place(size_t(P.I), -1);
   std::atomic<int64_t> total{0};
   std::atomic<const char *> bad{nullptr};
   for (int st = 0; st < 2; ++st) {
@@ -678,9 +679,15 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
         S.ga.size() != S.gb.size() || S.link.size() != S.term.size() || S.bw < 2 ||
         (S.bw & 1) || S.bw != P.cell[1 - st].bw)
       return "cell arrays";
-    on_threads(S.n_cells, 64, [&](int64_t k0, int64_t k1) {
+    // each storage layer's index in S.layer
+    for (size_t q = 0; q < S.layer.size(); ++q)
+      if (S.layer[q] >= 0) {
+        if (S.layer[q] >= P.I) return "cell layer";
+        place[size_t(S.layer[q])] = int32_t(q);
+      }
+    on_threads(S.n_cells, 16, [&](int64_t k0, int64_t k1) {
       auto fail = [&](const char *w) { bad = w; };
-      std::vector<int32_t> step_of, part_f, part_b;
+      std::vector<int32_t> step_of, part_f, part_b, chunk_of, chunk0;
       std::vector<std::pair<int32_t, int32_t>> wide;
       for (int64_t k = k0; k < k1; ++k) {
         const int32_t *r = &S.rec[12 * size_t(k)];
@@ -706,7 +713,8 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
         auto area = [&](int32_t j) { return gen ? int32_t(word(j, 0) >> 16) : j; };  // layer j's link
         // chunks: consecutive from the first layer on, inside their steps
         step_of.assign(size_t(nl), -1);
-        std::vector<int32_t> chunk_of(size_t(nl), -1), chunk0(size_t(nw), 0);
+        chunk_of.assign(size_t(nl), -1);
+        chunk0.assign(size_t(nw), 0);
         int32_t at_j = 0, s = -1;
         for (int32_t q = 0; q < nw; ++q) {
           const int32_t j0 = int32_t(work[q] & 0x1FFFu) * per, c = int32_t((work[q] >> 13) & 0x3FFu) * per;
@@ -726,17 +734,14 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
             return fail("cell layer");
           if (lay[j] < 0) continue;
           seen[size_t(lay[j])] = 1;
-          ++total;
         }
         // row parts: walks along the children cover each layer once; links and terms
         part_f.assign(size_t(nl), -1);
         part_b.assign(size_t(nl), -1);
-        std::vector<int32_t> at(static_cast<size_t>(nl));  // local layers by storage layer
-        std::iota(at.begin(), at.end(), 0);
-        std::sort(at.begin(), at.end(), [&](int32_t a, int32_t b) { return lay[a] < lay[b]; });
+        // a storage layer's place in this cell
         auto local = [&](int32_t L) {
-          const auto it = std::lower_bound(at.begin(), at.end(), L, [&](int32_t j, int32_t v) { return lay[j] < v; });
-          return it != at.end() && lay[*it] == L ? *it : -1;
+          const int32_t q = place[size_t(L)] - r[4];
+          return q >= 0 && q < nl && lay[q] == L ? q : -1;
         };
         int64_t walked = 0, layers = 0;
         for (int32_t q = 0; q < nrow; ++q) {
@@ -830,6 +835,7 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
           }
         }
         if (walked != layers) return fail("cell row part");
+        total += layers;
         std::sort(wide.begin(), wide.end());
         for (size_t q = 0; q < wide.size(); ++q)
           if (wide[q].first < nl + nrow * bwp || (q && wide[q - 1].first + wide[q - 1].second > wide[q].first))
