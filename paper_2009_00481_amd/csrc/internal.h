@@ -122,6 +122,8 @@ struct Problem {
   std::vector<int64_t> inst_var, inst_row;
 };
 
+constexpr size_t kScalBytes = 256;  // the solver's scalars (Dev::scal and what follows)
+
 // Byte offsets of the solver's arrays inside the device arena.
 struct ArenaLayout {
   size_t meta, child, parent, lam, mf, mbc, garcs, grec, gnb, rbeg, rin, rarc, canon_of, layer_of, layer_var, root_slot;

@@ -133,6 +133,8 @@ hipError_t launch_nonfinite(const Dev &D, const double *p, int64_t n, hipStream_
 // kLbStages where the terms take more than one workgroup).
 // which: 0 adds the min-plus constant D.lbc[0], 1 the smoothed one D.lbc[1].
 hipError_t launch_lb(const Dev &D, int nroot, int ncut, int which, hipStream_t s, int n = 1, int root_stride = 0);
+// D.scal[4] = the error words together, D.scal[5] = the bound in the history's slot.
+hipError_t launch_status(const Dev &D, const uint32_t *err0, const uint32_t *err1, int slot, hipStream_t s);
 hipError_t launch_set_counter(const Dev &D, long long value, hipStream_t s);
 // Per-instance bound of the last backward sweep (sum over the instance's rows of E^j, recomputed
 // from the messages and multipliers; instance k's constant term is added by the host).

@@ -1205,6 +1205,14 @@ __global__ void advance_counter_kernel(const Dev D, int n) {
   if (threadIdx.x == 0) *D.hist_n += n;
 }
 
+// what the host reads with one copy: the launches' error words and a bound of the history
+__global__ void status_kernel(const Dev D, const uint32_t *err0, const uint32_t *err1, int slot) {
+  if (threadIdx.x == 0) {
+    D.scal[4] = double(*err0 | *err1);
+    D.scal[5] = D.lb_hist[slot];
+  }
+}
+
 __global__ void set_counter_kernel(const Dev D, long long value) {
   if (threadIdx.x == 0) *D.hist_n = value;
 }
@@ -1527,6 +1535,11 @@ hipError_t launch_lb(const Dev &D, int nroot, int ncut, int which, hipStream_t s
   e = hipGetLastError();
   if (e != hipSuccess || n == 1) return e;
   hipLaunchKernelGGL(advance_counter_kernel, dim3(1), dim3(64), 0, s, D, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_status(const Dev &D, const uint32_t *err0, const uint32_t *err1, int slot, hipStream_t s) {
+  hipLaunchKernelGGL(status_kernel, dim3(1), dim3(64), 0, s, D, err0, err1, slot);
   return hipGetLastError();
 }
 

@@ -1459,8 +1459,8 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
   }
   A.root_e = take(4 * size_t(P.root_stride) * size_t(P.root_ring));
   A.cut_part = take(8 * size_t(P.n_cut_parts));
+  A.scal = take(kScalBytes);  // the history right behind, so that one copy reads both
   A.lb_hist = take(8 * size_t(P.hist_cap));
-  A.scal = take(256);
   A.inst_row = take(4 * P.inst_row32.size());
   A.inst_lb = take(8 * P.inst_lb_const.size());
   const size_t na = size_t(P.n_arcs_cut);

@@ -659,23 +659,30 @@ int32_t solver_set_graphs(Solver &S, int32_t enable) {
   return BDDMP_OK;
 }
 
+// The solver's scalars, and the bound history behind them if asked for, to out: one copy, since each
+// one into ordinary host memory waits for the device (about 10 us).
+int32_t read_status(Solver &S, double *out, bool history) {
+  const Plan &P = *S.plan;
+  const int slot = int((S.n_hist - 1) % P.hist_cap);
+  if (int32_t rc = launched(launch_status(S.D, S.pass[0].ctl + kPassErr, S.pass[1].ctl + kPassErr, slot, S.stream), "status"))
+    return rc;
+  const size_t bytes = history ? kScalBytes + 8 * size_t(P.hist_cap) : 48;
+  HIP_TRY(hipMemcpyAsync(out, S.D.scal, bytes, hipMemcpyDeviceToHost, S.stream), "hipMemcpyAsync");
+  HIP_TRY(hipStreamSynchronize(S.stream), "hipStreamSynchronize");
+  return pass_error(uint32_t(out[4]));
+}
+
 int32_t solver_lower_bound(Solver &S, double *lb, double *residual, double *any_lambda_bound) {
   const Plan &P = *S.plan;
-  double h = 0.0, sc[2] = {0.0, 0.0};
-  const int slot = int((S.n_hist - 1) % P.hist_cap);
-  HIP_TRY(hipMemcpyAsync(&h, S.D.lb_hist + slot, 8, hipMemcpyDeviceToHost, S.stream), "hipMemcpyAsync");
-  uint32_t err[2] = {0u, 0u};
-  for (int p = 0; p < 2; ++p)
-    HIP_TRY(hipMemcpyAsync(err + p, S.pass[p].ctl + kPassErr, 4, hipMemcpyDeviceToHost, S.stream), "hipMemcpyAsync");
-  if ((residual || any_lambda_bound) && P.n > 0) {
+  double sc[6];
+  const bool resid = (residual || any_lambda_bound) && P.n > 0;
+  if (resid)
     if (int32_t rc = launched(launch_residual(S.D, P.n, S.stream), "residual")) return rc;
-    HIP_TRY(hipMemcpyAsync(sc, S.D.scal, 16, hipMemcpyDeviceToHost, S.stream), "hipMemcpyAsync");
-  }
-  HIP_TRY(hipStreamSynchronize(S.stream), "hipStreamSynchronize");
-  if (int32_t rc = pass_error(err[0] | err[1])) return rc;
+  if (int32_t rc = read_status(S, sc, false)) return rc;
+  const double h = sc[5];
   if (lb) *lb = h;
-  if (residual) *residual = sc[0];
-  if (any_lambda_bound) *any_lambda_bound = h + sc[1];
+  if (residual) *residual = resid ? sc[0] : 0.0;
+  if (any_lambda_bound) *any_lambda_bound = h + (resid ? sc[1] : 0.0);
   if (!std::isfinite(h)) return set_error(BDDMP_NONFINITE, std::isnan(h) ? "lower bound is NaN" : "lower bound is infinite");
   return BDDMP_OK;
 }
@@ -697,14 +704,9 @@ int32_t solver_lb_history(Solver &S, double *out, int32_t cap, int32_t *n_out) {
   const Plan &P = *S.plan;
   const int64_t have = std::min<int64_t>(S.n_hist, P.hist_cap);
   const int64_t cnt = std::min<int64_t>(have, cap);
-  std::vector<double> ring(size_t(P.hist_cap));
-  HIP_TRY(hipMemcpyAsync(ring.data(), S.D.lb_hist, 8 * size_t(P.hist_cap), hipMemcpyDeviceToHost, S.stream),
-          "hipMemcpyAsync");
-  uint32_t err[2] = {0u, 0u};
-  for (int p = 0; p < 2; ++p)
-    HIP_TRY(hipMemcpyAsync(err + p, S.pass[p].ctl + kPassErr, 4, hipMemcpyDeviceToHost, S.stream), "hipMemcpyAsync");
-  HIP_TRY(hipStreamSynchronize(S.stream), "hipStreamSynchronize");
-  if (int32_t rc = pass_error(err[0] | err[1])) return rc;
+  std::vector<double> buf(kScalBytes / 8 + size_t(P.hist_cap));
+  if (int32_t rc = read_status(S, buf.data(), true)) return rc;
+  const double *ring = buf.data() + kScalBytes / 8;
   for (int64_t q = 0; q < cnt; ++q) {
     const int64_t idx = S.n_hist - cnt + q;
     out[q] = ring[size_t(idx % P.hist_cap)];
