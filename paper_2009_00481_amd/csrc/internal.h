@@ -47,7 +47,9 @@ constexpr int64_t kTileWideWork = 2048, kTileFewWork = 512;
 // nodes of a tile's general own levels, and of their child levels, that the node-parallel (flat)
 // path stages at most (kFlatCap / kTile per lane)
 constexpr int kFlatCap = 2048;
-constexpr int64_t kRowsMost = 8 << 20;   // layers up to which passes without updates run by rows
+// passes without updates run by rows in plans of up to kRowsMost layers and kRowWidest nodes a level
+constexpr int64_t kRowsMost = 8 << 20;
+constexpr int kRowWidest = 1024;
 // a general layer's word of its tile's maps: rank among the tile's general layers (bits 0-7), own nodes
 // before it (8-18), child nodes before it (19-31)
 constexpr uint32_t kMapOwnShift = 8, kMapOwnMask = 0x7FFu, kMapChildShift = 19;

@@ -73,9 +73,9 @@ struct Dev {
   const uint8_t *fgm, *bgm;
 };
 
-// Initial sweep (kBwd) or min-marginals to the outputs and messages (kFwd, as kExtract) of a plan of
-// narrow levels without cuts, one lane per row (m rows).
-hipError_t launch_rows(int dir, int m, const Dev &D, hipStream_t s);
+// Initial sweep (kBwd) or min-marginals to the outputs and messages (kFwd, as kExtract) of a plan without
+// cuts whose levels have at most width <= kRowWidest nodes, by its m rows.
+hipError_t launch_rows(int dir, int m, int width, const Dev &D, hipStream_t s);
 // One wave: nt normal tiles from tile0 of the pass's tile list (dir kFwd / kBwd, mode as above).
 // narrow_only selects the variant without wide levels, list the backward index-list variant.
 // kWrap: dir kFwd, narrow-only, no list.

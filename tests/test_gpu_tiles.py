@@ -81,3 +81,31 @@ def test_row_passes_bitwise(m, k):
         np.testing.assert_allclose(s.lb_history(1)[-1], o.lower_bound(), rtol=1e-12, atol=1e-9)
         s.iterate(1)
         o.iterate(1)
+
+
+@pytest.mark.parametrize("k,cmax,rhs", [(1, 2, 2), (6, 5, 9), (63, 3, 40), (64, 3, 40), (65, 3, 40), (130, 2, 70), (16, 200, 900)])
+@pytest.mark.parametrize("m", [1, 5])
+def test_wide_row_passes_bitwise(m, k, cmax, rhs):
+    """The same with levels of more than two nodes (up to some hundreds): one row per wavefront, 64 levels'
+    records at a time, more nodes than lanes."""
+    import torch
+
+    rng = np.random.default_rng([m, k, cmax])
+    rows = [(np.arange(j * (k - 1), j * (k - 1) + k) if k > 1 else np.array([j]), rng.integers(1, cmax + 1, k), 1, rhs)
+            for j in range(m)]
+    n = m * max(k - 1, 1) + 1
+    ilp = I.from_rows(n, rng.standard_normal(n, dtype=np.float32).astype(np.float64), rows)
+    plan = B.Plan(B.Problem.from_ilp(ilp))
+    lam = rng.standard_normal(int(plan.stats.n_incidences)).astype(np.float32)
+    s = B.Solver(plan)
+    s.set_lambda(torch.from_numpy(lam).cuda())
+    o = Oracle(I.ILP(ilp.n, ilp.cost, ilp.row_ptr, ilp.col, ilp.coef, ilp.sense, ilp.rhs, plan.order()), precision="f32")
+    o.init()
+    o.set_lambda(lam.astype(np.float64))
+    for step in range(2):
+        m0, m1 = s.min_marginals()
+        r0, r1 = o.min_marginals()
+        assert np.array_equal(m0.cpu().numpy().astype(np.float64), r0) and np.array_equal(m1.cpu().numpy().astype(np.float64), r1)
+        np.testing.assert_allclose(s.lb_history(1)[-1], o.lower_bound(), rtol=1e-12, atol=1e-9)
+        s.iterate(1)
+        o.iterate(1)
