@@ -8,7 +8,8 @@ separately and not part of a step.
 
 value = BDD arc-updates per second = 2 * live arcs * T per step / step time (each live arc is
 relaxed and marginalised once per pass). The roofline object prices the dominant wave kernel's
-algorithmic bytes (20 per node and 8 per incidence per pass) against MI355X HBM peak; cpu_baseline
+algorithmic bytes (20 per node and 8 per incidence per pass) against MI355X HBM peak, or, where the run
+used cell launches, the 8 bytes a layer that those move per iteration; cpu_baseline
 is the fp64 CPU oracle on the same instance, one thread, on a bounded sample of iterations.
 
 smoothed_vs_plain: the differentiable form (smoothed iterations with checkpoints, then the adjoint
@@ -48,7 +49,8 @@ def log(*a):
 
 
 KERNEL_SOURCES = ["paper_2009_00481_amd/csrc/kernels.hip", "paper_2009_00481_amd/csrc/kernels.h",
-                  "paper_2009_00481_amd/csrc/device.h",
+                  "paper_2009_00481_amd/csrc/device.h", "paper_2009_00481_amd/csrc/cells.hip",
+                  "paper_2009_00481_amd/csrc/cells.cpp",
                   "paper_2009_00481_amd/csrc/plan.cpp", "paper_2009_00481_amd/csrc/internal.h"]
 
 
@@ -93,6 +95,16 @@ def roofline_of(kt, traffic_rec, kernel="wave_kernel"):
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "traffic_unit": "bytes/launch",
             "kernel": kname, "bytes_per_launch": kb / kl, "avg_launch_us": kms / kl * 1e3,
             "both_passes_gbs": round((kt["fwd_bytes"] + kt["bwd_bytes"]) / ((kt["fwd_ms"] + kt["bwd_ms"]) * 1e-3) / 1e9, 1)}
+
+
+def cell_roofline(n_layers: int, iter_ms: float):
+    """Cell launches: two per iteration, which together read and write every layer's multiplier once (8
+    bytes a layer; the messages stay in LDS), so their rate says how far from HBM they are bound: by
+    instruction issue and LDS round trips."""
+    achieved = 8.0 * n_layers / (iter_ms * 1e-3) / 1e9
+    return {"bound": "instruction issue and LDS latency", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+            "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "traffic_unit": "bytes/launch",
+            "kernel": "cell_kernel", "bytes_per_launch": 4.0 * n_layers, "avg_launch_us": iter_ms * 1e3 / 2}
 
 
 def oracle_bounds(workload: str, T: int):
@@ -495,6 +507,12 @@ def main():
     gbps_iter = iter_bytes / (iter_ms * 1e-3) / 1e9 if iter_ms > 0 else None
 
     roofline = roofline_of(kt, committed_traffic(args.workload, tprefix), kname)
+    # the pass times above are the wave kernels'; an iteration well below them ran as cell launches
+    wave_roofline = None
+    step_iter_ms = ms_per_step / T
+    cells = launch == "waves" and step_iter_ms < 0.8 * (kt["fwd_ms"] + kt["bwd_ms"]) / args.profile_iters
+    if cells:
+        wave_roofline, roofline = roofline, cell_roofline(int(st.n_incidences), step_iter_ms)
 
     # time to bound: first t with LB_t >= LB* - 1e-4 max(|LB*|, 1). LB* is the fp64 oracle's LB_T on
     # the same instance when it is stored for T iterations, else this run's own LB_T. Measured with
@@ -588,7 +606,7 @@ def main():
                    "n_bdds": int(st.n_bdds), "n_nodes": int(st.n_nodes), "n_incidences": int(st.n_incidences),
                    "n_arcs_live": int(st.n_arcs_live), "waves_per_pass": [int(st.waves_fwd), int(st.waves_bwd)],
                    "bound_dtype": "f64",
-                   "launch": {"waves": "one launch per wave (launch mode 0)",
+                   "launch": {"waves": "cell launches (launch mode 0)" if cells else "one launch per wave (launch mode 0)",
                               "wave_groups": "every wave of a pass in one wave-group launch (launch mode 3)",
                               "wave_group_pairs": "every wave of a pass in one wave-group launch, two tiles per "
                                                   "workgroup (launch mode 4)"}[launch]},
@@ -600,7 +618,7 @@ def main():
         "bound_vs_oracle": vs_oracle, "lb_final": lb_self, "lb_0": float(hist[0]),
         "primal_obj": obj, "primal_violated_rows": int(nviol), "primal_search": search,
         "host_build_s": {"generate": gen_s, "plan": plan_s, "bind_upload": bind_s},
-        "roofline": roofline, "cpu_baseline": cpu,
+        "roofline": roofline, "wave_launch_roofline": wave_roofline, "cpu_baseline": cpu,
         "batched_vs_plain": batched,
         "smoothed_vs_plain": smoothed,
         "split_vs_plain": split,

@@ -322,7 +322,7 @@ struct WaveLds {
 // Narrow layers run one per lane. General layers (a level or its child level wider than 2) are
 // collected per tile and run either node-parallel over the whole tile (flat path) or by groups of
 // G lanes, as the tile's width class selects.
-// w0, end: the tile's start and end words (positions with the width class and root bits).
+// w0, end: the tile's start and end words (positions with the width class).
 // list: with LIST, whether this tile's positions go through bwd_list (callers that decide per tile
 // instantiate LIST true and pass the tile's flag; the wave launches leave it true).
 // COH: messages of this pass are read and written coherently (dataflow launch; see msg_ld).
