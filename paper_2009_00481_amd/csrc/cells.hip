@@ -18,7 +18,7 @@
 // iterate the multipliers are in storage order; inside a run they are kept in cell order, where a
 // cell's are contiguous. Measured, us per iteration against one launch per wave replayed as a graph:
 // Potts 256x256x8 168 (367), 128x128x4 29 (61), 16x16x4 15 (49); Potts 8x8x3, whole in one workgroup, 10
-// (38); a batch of 32 tracking instances of 200 to 1967 detections 141 (1040).
+// (38); a batch of 32 tracking instances of 200 to 1967 detections 133 (1040).
 #include <hip/hip_runtime.h>
 
 #include <cmath>

@@ -1115,7 +1115,9 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
   // work; where they do not, a wave takes one tile's latency, which grows with its nodes, so the wave is
   // split further, down to kTileFewWork. Measured, us per iteration with 2048 / 1024 / 512 / 256 nodes,
   // one launch per wave: tomography P = 64 3111 / 2716 / 2493 / 2462, P = 80 4017 / 3479 / 3258 / 3236, 16
-  // instances 2979 / 2588 / 2382 / 2340; 256 instances with wave groups 8730 / 9710 (1536) / 12250 / -.
+  // instances 2979 / 2588 / 2382 / 2340; 256 instances with wave groups 8730 / 9710 (1536) / 12250 / -. With
+  // the tiles' later changes, 1024 / 512 / 256: P = 64 2261 / 1980 / 1949, P = 80 2895 / 2624 / 2596, 16 instances
+  // 2254 / 1973 / 1925.
   auto budget = [&](const std::vector<int32_t> &vars) {
     if (opt.tile_work > 0) return P.tile_work;
     int64_t work = 0;
