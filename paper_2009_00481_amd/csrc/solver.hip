@@ -1032,16 +1032,22 @@ int32_t solver_smooth_run(Solver &S, float alpha, int32_t T, void *ws, size_t by
   S.n_hist++;
   S.iters = 0;
   HIP_TRY(copy_f(w.ckpt, S.D.lam, P.I, S.stream), "hipMemcpyAsync");
-  // an iteration reads checkpoint t and leaves its multipliers in checkpoint t + 1
-  for (int32_t t = 0; t < T; ++t) {
-    const Dev D = with(S.D, w.ckpt + I1 * size_t(t + 1), S.D.mbc);
-    A.lam_in = w.ckpt + I1 * size_t(t);
-    if (int32_t rc = smooth_pass(S, D, kFwd, kUpdate, false, A)) return rc;
-    A.lam_in = D.lam;
-    if (int32_t rc = smooth_pass(S, D, kBwd, kUpdate, false, A)) return rc;
-    if (int32_t rc = enqueue_lb(S, nullptr, S.stream, 1)) return rc;
-    S.n_hist++;
-    S.iters++;
+  // an iteration reads checkpoint t and leaves its multipliers in checkpoint t + 1, and its bound terms in
+  // the ring, whose bounds are summed together
+  for (int32_t t = 0; t < T;) {
+    const int32_t k = std::min(T - t, P.root_ring);
+    for (int32_t q = 0; q < k; ++q) {
+      Dev D = with(S.D, w.ckpt + I1 * size_t(t + q + 1), S.D.mbc);
+      D.root_e += size_t(q) * size_t(P.root_stride);
+      A.lam_in = w.ckpt + I1 * size_t(t + q);
+      if (int32_t rc = smooth_pass(S, D, kFwd, kUpdate, false, A)) return rc;
+      A.lam_in = D.lam;
+      if (int32_t rc = smooth_pass(S, D, kBwd, kUpdate, false, A)) return rc;
+    }
+    if (int32_t rc = launched(launch_lb(S.D, P.n_root, 0, 1, S.stream, k, P.root_stride), "bound reduction")) return rc;
+    S.n_hist += k;
+    S.iters += k;
+    t += k;
   }
   if (T) HIP_TRY(copy_f(S.D.lam, w.ckpt + I1 * size_t(T), P.I, S.stream), "hipMemcpyAsync");
   return BDDMP_OK;
