@@ -551,6 +551,11 @@ int32_t solver_bind(const Plan &P, void *arena, size_t bytes, void *stream, Solv
       up(A.fgm, P.fgm.data(), P.fgm.size()),
       up(A.bgm, P.bgm.data(), P.bgm.size()),
   };
+  for (hipError_t e : errs)
+    if (e != hipSuccess) {
+      delete S;
+      return hip_fail(e, "hipMemcpyAsync (upload)");
+    }
   for (int q = 0; q < 2; ++q) {
     const CellStage &c = P.cell[q];
     auto bytes = [](const auto &v) { return std::make_pair(static_cast<const void *>(v.data()), 4 * v.size()); };
