@@ -56,6 +56,7 @@ struct Solver {
   bool group_pairs = false;
   uint32_t group_spin = 0;
   CellArgs cell[2]{};  // cell launches of stages A and B (plans with cells)
+  bool tuning = false;  // autotune is timing the general-layer paths, which cells have none of
   ~Solver() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (gexec_wrap) (void)hipGraphExecDestroy(gexec_wrap);
@@ -103,7 +104,7 @@ bool use_wrap(const Solver &S) { return S.plan->fuse_wrap && !S.dataflow && !S.p
 
 // cell launches: the default launch form's replayed iterations on plans with cells
 int cell_kind(const Solver &S) {
-  return S.use_graph && !S.dataflow && !S.pipe && !S.group_waves ? S.plan->cell_kind : 0;
+  return S.use_graph && !S.tuning && !S.dataflow && !S.pipe && !S.group_waves ? S.plan->cell_kind : 0;
 }
 
 // NONFINITE unless every value of the device arrays (float or double, n each) is finite; checked on
@@ -850,7 +851,8 @@ int32_t solver_get_groups(const Solver &S, int32_t *lanes) {
 // Coordinate search over the general-layer path: for each width class that has tiles, time iters
 // iterations with the node-parallel path and with groups of every power of two from 1 to 64 lanes
 // (the other classes at their current choice) and keep the fastest. Every choice computes the same values (min is exact), so only
-// time differs; the solver advances by the iterations run.
+// time differs; the solver advances by the iterations run. Plans with cells are timed without them: the
+// choice serves their other launch forms.
 int32_t solver_autotune(Solver &S, int32_t iters, int32_t *lanes) {
   const Plan &P = *S.plan;
   if (iters < 1) return set_error(BDDMP_INVALID_ARG, "iters must be positive");
@@ -858,6 +860,7 @@ int32_t solver_autotune(Solver &S, int32_t iters, int32_t *lanes) {
   HIP_TRY(hipEventCreate(&a), "hipEventCreate");
   HIP_TRY(hipEventCreate(&b), "hipEventCreate");
   int32_t rc = BDDMP_OK;
+  S.tuning = true;
   for (int c = 0; c < kWidthClasses && !rc; ++c) {
     if (!P.class_tiles[c]) continue;
     uint32_t best_lg = (S.D.gsel >> (4 * c)) & 0xFu;
@@ -879,6 +882,7 @@ int32_t solver_autotune(Solver &S, int32_t iters, int32_t *lanes) {
     }
     S.D.gsel = (S.D.gsel & ~(0xFu << (4 * c))) | (best_lg << (4 * c));
   }
+  S.tuning = false;
   (void)hipEventDestroy(a);
   (void)hipEventDestroy(b);
   if (rc) return rc;

@@ -34,3 +34,25 @@ print(n, missed)
     n, missed = out.split(None, 1)
     assert int(n) > 20
     assert missed.strip() == "[]"
+
+
+@pytest.mark.parametrize("launch", [(0, 0), (3, 4)])
+def test_autotune_times_the_paths_it_chooses_between(stub, launch):
+    """Cells have no general-layer path: a plan that runs as cells is tuned on its wave launches, or on the
+    selected form's, and runs as cells again afterwards."""
+    out = hip_stub.run(stub, f"""
+plan = B.Plan(B.Problem.from_ilp(I.tracking(1400, seed=1)))
+h = bind(plan)
+if {launch[0]}:
+    B.bddmp_solver_set_launch(h, *{launch})
+launches()
+B.bddmp_solver_autotune(h, 2)
+tuned = launches()
+B.bddmp_solver_iterate(h, 2)
+after = launches()
+for name in (tuned, after):
+    print(*(sum(k in q for q in name) for k in ("cell_kernel", "wave_kernel", "group_kernel")))
+""")
+    tuned, after = ([int(v) for v in line.split()] for line in out.splitlines())
+    assert tuned[0] == 0 and max(tuned[1:]) > 0
+    assert (after[0] > 0) == (launch[0] == 0)
