@@ -56,6 +56,7 @@ struct Solver {
   bool group_pairs = false;
   uint32_t group_spin = 0;
   CellArgs cell[2]{};  // cell launches of stages A and B (plans with cells)
+  bool cells_fit = false;  // the plan has cells and the device's workgroups hold the largest
   bool tuning = false;  // autotune is timing the general-layer paths, which cells have none of
   ~Solver() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
@@ -104,7 +105,7 @@ bool use_wrap(const Solver &S) { return S.plan->fuse_wrap && !S.dataflow && !S.p
 
 // cell launches: the default launch form's replayed iterations on plans with cells
 int cell_kind(const Solver &S) {
-  return S.use_graph && !S.tuning && !S.dataflow && !S.pipe && !S.group_waves ? S.plan->cell_kind : 0;
+  return S.cells_fit && S.use_graph && !S.tuning && !S.dataflow && !S.pipe && !S.group_waves ? S.plan->cell_kind : 0;
 }
 
 // NONFINITE unless every value of the device arrays (float or double, n each) is finite; checked on
@@ -501,6 +502,19 @@ int32_t solver_bind(const Plan &P, void *arena, size_t bytes, void *stream, Solv
     pa.n_tiles = int32_t((p ? P.btinfo : P.ftinfo).size());
     pa.chunk = 1;
     pa.spin_limit = kPassSpinLimit;
+  }
+
+  // the plan sizes cells for the 160 KB of LDS a gfx950 workgroup may take; where the device gives less
+  // than a cell needs, its iterations run as wave launches
+  if (P.cell_kind) {
+    int dev = 0, most = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&most, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    if (e != hipSuccess) {
+      delete S;
+      return hip_fail(e, "hipDeviceGetAttribute (LDS of a workgroup)");
+    }
+    S->cells_fit = std::max(P.cell[0].lds, P.cell[1].lds) <= most;
   }
 
   auto up = [&](size_t off, const void *src, size_t nbytes) -> hipError_t {

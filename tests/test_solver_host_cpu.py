@@ -56,3 +56,25 @@ for name in (tuned, after):
     tuned, after = ([int(v) for v in line.split()] for line in out.splitlines())
     assert tuned[0] == 0 and max(tuned[1:]) > 0
     assert (after[0] > 0) == (launch[0] == 0)
+
+
+@pytest.mark.parametrize("kib,cells", [(160, True), (64, False)])
+def test_cells_run_where_the_device_holds_them(stub, kib, cells):
+    """A cell of this plan takes 138 KB of LDS: on a device with less to a workgroup the iterations run as
+    wave launches, as they do without cells."""
+    out = hip_stub.run(stub, f"""
+plan = B.Plan(B.Problem.from_ilp(I.tracking(1400, seed=1)))
+stub.stub_set_lds({kib} << 10)
+h = bind(plan)
+launches()
+B.bddmp_solver_iterate(h, 3)
+print(*(sum(k in q for q in launches()) for k in ("cell_kernel", "wave_kernel")))
+# (a plan whose cells are small)
+small = B.Plan(B.Problem.from_ilp(I.potts_grid(3, 3, 2, seed=1)))
+h = bind(small)
+launches()
+B.bddmp_solver_iterate(h, 3)
+print(sum("cell_kernel" in q for q in launches()))
+""").split()
+    assert (int(out[0]) > 0) == cells and (int(out[1]) > 0) == (not cells)
+    assert int(out[2]) > 0
