@@ -68,7 +68,8 @@ stub.stub_set_lds({kib} << 10)
 h = bind(plan)
 launches()
 B.bddmp_solver_iterate(h, 3)
-print(*(sum(k in q for q in launches()) for k in ("cell_kernel", "wave_kernel")))
+names = launches()
+print(*(sum(k in q for q in names) for k in ("cell_kernel", "wave_kernel")))
 # (a plan whose cells are small)
 small = B.Plan(B.Problem.from_ilp(I.potts_grid(3, 3, 2, seed=1)))
 h = bind(small)
