@@ -47,9 +47,11 @@ constexpr int64_t kTileWideWork = 2048, kTileFewWork = 512;
 // nodes of a tile's general own levels, and of their child levels, that the node-parallel (flat)
 // path stages at most (kFlatCap / kTile per lane)
 constexpr int kFlatCap = 2048;
-// passes without updates run by rows in plans of up to kRowsMost layers and kRowWidest nodes a level
+// passes without updates run by rows (Plan::by_rows) in plans of up to kRowsMost layers and kRowWidest nodes
+// a level, where that takes less than a launch per wave
 constexpr int64_t kRowsMost = 8 << 20;
 constexpr int kRowWidest = 1024;
+constexpr int kRowLine = 16, kRowSample = 256;
 // a general layer's word of its tile's maps: rank among the tile's general layers (bits 0-7), own nodes
 // before it (8-18), child nodes before it (19-31)
 constexpr uint32_t kMapOwnShift = 8, kMapOwnMask = 0x7FFu, kMapChildShift = 19;
@@ -287,6 +289,7 @@ struct Plan {
   uint32_t gsel = kDefaultGsel;
   int64_t tile_work = kTileWideWork;
   int64_t class_tiles[kWidthClasses] = {0, 0, 0, 0};
+  bool by_rows = false;  // the passes without updates run by rows
   // cell launches (cells.cpp): 0 none; 1 every instance component in one workgroup; 2 two stages
   // (A = a prefix of each instance's order, B = the rest)
   int32_t cell_kind = 0, n_comp = 0;

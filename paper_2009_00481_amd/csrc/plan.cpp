@@ -577,6 +577,45 @@ std::string validate_layout(const Plan &P, const std::vector<int32_t> &ownw, con
 
 }  // namespace
 
+// Cache lines (of kRowLine layers' words) that a narrow plan's row passes fetch beyond those of contiguous
+// layers: the distinct ones of each workgroup's rows, counted over up to kRowSample workgroups spread over
+// the plan and scaled to it.
+static double extra_lines(const Plan &P) {
+  const int64_t m = P.m, blocks = (m + kTile - 1) / kTile, step = (blocks + kRowSample - 1) / kRowSample;
+  std::vector<int32_t> line;
+  int64_t lines = 0, seen = 0;
+  for (int64_t b = 0; b < blocks; b += step) {
+    const int64_t c0 = P.canon_off[kTile * b], c1 = P.canon_off[std::min(m, kTile * (b + 1))];
+    line.clear();
+    for (int64_t c = c0; c < c1; ++c) line.push_back(P.layer_of[c] / kRowLine);
+    std::sort(line.begin(), line.end());
+    lines += std::unique(line.begin(), line.end()) - line.begin();
+    seen += c1 - c0;
+  }
+  return seen ? double(P.I) * (double(lines) / double(seen) - 1.0 / kRowLine) : 0.0;
+}
+
+// Whether passes without updates (initial sweep, min-marginals) run by rows in one launch, a lane or (plans
+// with levels of more than two nodes) a wavefront each, instead of one launch per wave. A launch per wave
+// costs about 3.5 us a wave (5 on general levels) and reads its layers in runs; by rows nothing waits for a
+// wave, but the layers of narrow rows are gathered, each extra line at a cost (about 45 us a million), and a
+// wide row's levels run one after another (200 us more a million layers, 10 to 20 less a million nodes).
+// Measured, min-marginals in us by waves / by rows:
+//   narrow: Potts 128x128x4 (8 waves) 48 / 25, 160x160x8 (16) 223 / 198, 600x600x2 (4, 9.3 million layers) 146
+//     / 148, 256x256x8 (16, 19.3 million) 515 / 536; random rows of 2 (2 waves), 0.1 million layers 17 / 11,
+//     0.4 million 18 / 33, 3.6 million 122 / 320; rows of 8 (8 waves), 0.4 million 35 / 24, 1.6 million 73 /
+//     126; rows of 40 (40 waves), 1.6 million 162 / 113, 6 million 300 / 524; graph matching 5000 (23 waves,
+//     1.5 million) 92 / 60
+//   wide: tomography 64 (205 waves) 1016 / 180, eight of them (1.9 million) 1101 / 539; knapsack rows of 5 (5
+//     waves, 2 nodes a level), 0.1 million 28 / 29, 0.3 million 28 / 71; rows of 20 (20 waves), a million
+//     layers of 4 nodes 155 / 190 (initial sweep 177 / 153), of 20 nodes 466 / 206
+// The initial sweep's figures cross at about the same sizes.
+static bool rows_pay(const Plan &P) {
+  if (P.n_cuts || P.I > kRowsMost || P.max_width > kRowWidest) return false;
+  if (P.n_general) return double(P.I) <= 20e3 * P.Df + 0.1 * double(P.N);
+  return double(P.I) <= 78e3 * P.Df || extra_lines(P) <= 78e3 * P.Df;
+}
+
 int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
   P = Plan{};
   const int32_t n = p.n;
@@ -1038,6 +1077,7 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
     P.bdd_canon_off[j + 1] = int32_t(P.canon_off[j + 1]);
     if (P.canon_off[j + 1] > P.canon_off[j]) P.root_slot[j] = int32_t(P.own_slot[P.layer_of[P.canon_off[j]]]);
   }
+  P.by_rows = rows_pay(P);
 
   // cut tables: arcs and live pairs numbered in canonical (row, level) order; the cut records list
   // the narrow cuts (both levels at most 2 nodes, one lane each) first, then the wide ones (one

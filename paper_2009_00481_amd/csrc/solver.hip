@@ -276,21 +276,11 @@ int32_t enqueue_copy_bwd(Solver &S, int update, hipStream_t st) {
                   "copy-arc update");
 }
 
-// Whether passes without updates (initial sweep, min-marginals) run by rows in one launch, a lane or (plans
-// with levels of more than two nodes) a wavefront each, instead of one launch per wave: plans without cuts,
-// while what a row's lanes gather (about 20 bytes a layer) stays in the 256 MB last-level cache; beyond,
-// the waves' contiguous reads are faster. Measured, us by rows / by waves, initial sweep from given
-// multipliers and min-marginals: Potts 8x8x3 34 / 79 and 10 / 29, graph matching 5000 (1.5 million layers)
-// 76 / 136 and 59 / 99, Potts 128x128x8 (4.8 million) 114 / 137 and 98 / 146, 256x256x8 (19.3 million) 443 /
-// 380 and 536 / 515; tomography 64 127 / 1517 and 182 / 1623, 36 instances of tomography and tracking (7.3
-// million) 1364 / 3285 and 2001 / 3604 (wider plans lose about 190 us a million layers by rows).
-bool by_rows(const Plan &P) { return P.n_cuts == 0 && P.I <= kRowsMost && P.max_width <= kRowWidest; }
-
 // most nodes of a level, 2 for plans of narrow levels (which have no general records)
 int row_width(const Plan &P) { return P.n_general ? P.max_width : 2; }
 
 int32_t initial_sweep(Solver &S) {
-  if (by_rows(*S.plan)) {
+  if (S.plan->by_rows) {
     if (int32_t rc = launched(launch_rows(kBwd, S.plan->m, row_width(*S.plan), S.D, S.stream), "row sweep")) return rc;
   } else if (int32_t rc = run_pass(S, kBwd, kNoUpdate, nullptr, S.stream)) {
     return rc;
@@ -743,7 +733,7 @@ int32_t solver_lb_history(Solver &S, double *out, int32_t cap, int32_t *n_out) {
 int32_t solver_min_marginals(Solver &S, float *m0, float *m1) {
   S.D.out0 = m0;
   S.D.out1 = m1;
-  const int32_t rc = by_rows(*S.plan) ? launched(launch_rows(kFwd, S.plan->m, row_width(*S.plan), S.D, S.stream), "row min-marginals")
+  const int32_t rc = S.plan->by_rows ? launched(launch_rows(kFwd, S.plan->m, row_width(*S.plan), S.D, S.stream), "row min-marginals")
                                       : run_pass(S, kFwd, kExtract, nullptr, S.stream);
   S.D.out0 = S.D.out1 = nullptr;
   return rc;
@@ -988,7 +978,7 @@ SmoothWs smooth_layout(const Plan &P, int32_t T, char *base) {
 
 int32_t smooth_pass(Solver &S, const Dev &D, int dir, int mode, bool adjoint, const SmoothArgs &A) {
   const Plan &P = *S.plan;
-  if (mode == kNoUpdate && !adjoint && P.n_general == 0 && by_rows(P))
+  if (mode == kNoUpdate && !adjoint && P.n_general == 0 && P.by_rows)
     return launched(launch_smooth_rows(P.m, D, A.alpha, S.stream), "smoothed row sweep");
   const auto &waves = dir == kFwd ? P.fwd_waves : P.bwd_waves;
   const int nw = int(waves.size());
