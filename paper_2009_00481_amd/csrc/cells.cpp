@@ -320,9 +320,29 @@ struct CellBuilder {
 
   bool same_stage(int32_t L, uint8_t st) const { return L >= 0 && P.var_stage[size_t(P.layer_var[size_t(L)])] == st; }
 
-  // vars: the cell's variables by (step, storage); layer (when asked): the storage layer of each local
+  // layers (with pads) and row parts of the cell of these variables; false when they are too many
+  bool measure(const int32_t *vars, size_t nv, int32_t &nl, int32_t &nrow) const {
+    const uint8_t st = nv ? P.var_stage[size_t(vars[0])] : 0;
+    int32_t j = 0, s0 = 0, cur = -1;
+    nl = nrow = 0;
+    for (size_t k = 0; k < nv; ++k) {
+      const int32_t i = vars[k], nj = P.var_nj[size_t(i)];
+      if (vstep[size_t(i)] != cur) {
+        cur = vstep[size_t(i)];
+        s0 = j;
+      }
+      if (((j - s0) & 63) + nj > 64) j = s0 + ((j - s0 + 63) & ~63);
+      j += nj;
+      if (j >= kCellMaxLayers) return false;
+      for (int32_t q = 0; q < nj; ++q) nrow += !same_stage(P.parent[size_t(P.var_first[size_t(i)] + q)], st);
+    }
+    nl = (j + 3) & ~3;
+    return true;
+  }
+
+  // vars: the cell's variables by (step, storage), as measured; layer: the storage layer of each local
   // one. False when the program's fields overflow.
-  bool build(const int32_t *vars, size_t nv, CellProg &C, std::vector<int32_t> *layer = nullptr) const {
+  bool build(const int32_t *vars, size_t nv, CellProg &C, int32_t *layer) const {
     C.clear();
     // local indices: steps one after another, a variable's layers never across a 64-lane boundary of
     // its step (pads hold no layer)
@@ -339,7 +359,6 @@ struct CellBuilder {
       at[k] = j;
       for (int32_t q = 0; q < nj; ++q) loc[size_t(P.var_first[size_t(i)] + q)] = uint16_t(j + q);
       j += nj;
-      if (j >= kCellMaxLayers) return false;
     }
     const bool wide_plan = P.max_width > 2;
     C.nl = (j + 3) & ~3;
@@ -353,7 +372,6 @@ struct CellBuilder {
       C.own.assign(size_t(C.nl), 0u);
       C.arc.assign(4 * size_t(C.nl), 0u);
     }
-    if (layer) layer->assign(size_t(C.nl), -1);
     auto each = [&](auto &&f) {
       for (size_t k = 0; k < nv; ++k)
         for (int32_t q = 0; q < P.var_nj[size_t(vars[k])]; ++q) f(vars[k], q, P.var_first[size_t(vars[k])] + q, at[k] + q);
@@ -415,7 +433,7 @@ struct CellBuilder {
       if (last) r |= kCellRowLast | (x0 ? kCellRowTermX : 0u) | (y0 ? kCellRowTermY : 0u);
       C.h[size_t(jj)] = h;
       C.w1[size_t(jj)] = w1;
-      if (layer) (*layer)[size_t(jj)] = L;
+      layer[jj] = L;
     });
     return true;
   }
@@ -524,7 +542,7 @@ bool build_cells(Plan &P, const std::vector<int64_t> &iptr, const std::vector<in
       fill += clayers[size_t(c)];
     }
     S.n_cells = nc;
-    // each cell's variables, by step, then storage
+    // each cell's variables, by step (below), then storage
     std::vector<int64_t> vp(size_t(nc) + 1, 0);
     for (int32_t i = 0; i < n; ++i)
       if (P.var_comp[size_t(i)] >= 0 && P.var_stage[size_t(i)] == st) vp[size_t(cell_of[size_t(P.var_comp[size_t(i)])]) + 1]++;
@@ -532,67 +550,79 @@ bool build_cells(Plan &P, const std::vector<int64_t> &iptr, const std::vector<in
     std::vector<int32_t> vars(static_cast<size_t>(vp[size_t(nc)]));
     {
       std::vector<int64_t> at(vp.begin(), vp.end() - 1);
-      for (int32_t i = 0; i < n; ++i)
-        if (P.var_comp[size_t(i)] >= 0 && P.var_stage[size_t(i)] == st)
-          vars[size_t(at[size_t(cell_of[size_t(P.var_comp[size_t(i)])])]++)] = i;
+      for (int64_t L = 0; L < P.I; L += P.var_nj[size_t(P.layer_var[size_t(L)])]) {
+        const int32_t i = P.layer_var[size_t(L)];
+        if (P.var_stage[size_t(i)] == st) vars[size_t(at[size_t(cell_of[size_t(P.var_comp[size_t(i)])])]++)] = i;
+      }
     }
     auto nvars = [&](int64_t k) { return size_t(vp[size_t(k) + 1] - vp[size_t(k)]); };
-    std::vector<uint64_t> hash(size_t(nc), 0);
-    std::vector<int32_t> size_of(size_t(nc), 0), rows_of(size_t(nc), 0);
+    // sizes of the cells, and where each one's layers and row parts start
+    std::vector<int64_t> lbase(size_t(nc) + 1, 0), rbase(size_t(nc) + 1, 0);
     std::atomic<bool> ok{true}, all_pairs{true};
-    on_threads(nc, 64, [&](int64_t k0, int64_t k1) {
-      CellProg C;
+    // cells to a host thread: about as many layers in all, however large the cells
+    const int64_t share = std::max<int64_t>(1, int64_t(nc) * 16384 / std::max<int64_t>(total, 1));
+    on_threads(nc, share, [&](int64_t k0, int64_t k1) {
+      std::vector<int32_t> at, by;
       for (int64_t k = k0; k < k1; ++k) {
         int32_t *v = vars.data() + vp[size_t(k)];
-        std::sort(v, v + nvars(k), [&](int32_t a, int32_t b) {
-          return vstep[size_t(a)] != vstep[size_t(b)] ? vstep[size_t(a)] < vstep[size_t(b)]
-                                                      : P.var_first[size_t(a)] < P.var_first[size_t(b)];
-        });
-        if (!B.build(v, nvars(k), C)) ok = false;
-        if (!C.pairs) all_pairs = false;
-        hash[size_t(k)] = C.hash();
-        size_of[size_t(k)] = C.nl;
-        rows_of[size_t(k)] = int32_t(C.row.size());
+        // stable counting sort by step
+        at.assign(1, 0);
+        for (size_t q = 0; q < nvars(k); ++q) {
+          const size_t t = size_t(vstep[size_t(v[q])]) + 1;
+          if (t >= at.size()) at.resize(t + 1, 0);
+          ++at[t];
+        }
+        for (size_t t = 1; t < at.size(); ++t) at[t] += at[t - 1];
+        by.resize(nvars(k));
+        for (size_t q = 0; q < by.size(); ++q) by[size_t(at[size_t(vstep[size_t(v[q])])]++)] = v[q];
+        std::copy(by.begin(), by.end(), v);
+        int32_t nl = 0, nrow = 0;
+        if (!B.measure(v, nvars(k), nl, nrow)) ok = false;
+        lbase[size_t(k) + 1] = nl;
+        rbase[size_t(k) + 1] = nrow;
       }
     });
     if (!ok) return false;
-    // cells with equal programs share one (by hash, then verified; a collision gets its own)
-    std::vector<CellProg> prog;
-    std::vector<int32_t> tmpl(size_t(nc), -1);
-    std::unordered_map<uint64_t, int32_t> by_hash;
-    auto append = [&](int64_t k) {
-      prog.emplace_back();
-      B.build(vars.data() + vp[size_t(k)], nvars(k), prog.back());
-      tmpl[size_t(k)] = int32_t(prog.size()) - 1;
-    };
     for (int32_t k = 0; k < nc; ++k) {
-      auto it = by_hash.find(hash[size_t(k)]);
-      if (it == by_hash.end()) {
-        append(k);
-        by_hash.emplace(hash[size_t(k)], tmpl[size_t(k)]);
-      } else {
-        tmpl[size_t(k)] = it->second;
-      }
-    }
-    // per cell: storage layers in cell order, the row parts' bound terms, and where they start (B) or
-    // end (A), for the links
-    std::vector<int64_t> lbase(size_t(nc) + 1, 0), rbase(size_t(nc) + 1, 0);
-    for (int32_t k = 0; k < nc; ++k) {
-      lbase[size_t(k) + 1] = lbase[size_t(k)] + size_of[size_t(k)];
-      rbase[size_t(k) + 1] = rbase[size_t(k)] + rows_of[size_t(k)];
+      lbase[size_t(k) + 1] += lbase[size_t(k)];
+      rbase[size_t(k) + 1] += rbase[size_t(k)];
     }
     if (lbase[size_t(nc)] >= INT32_MAX / 2 || rbase[size_t(nc)] * bw >= INT32_MAX / 2) return false;
     S.layer.assign(size_t(lbase[size_t(nc)]), -1);
     S.link.assign(size_t(rbase[size_t(nc)]), -1);
     S.term.assign(size_t(rbase[size_t(nc)]), -1);
-    std::vector<uint8_t> differs(size_t(nc), 0);
-    on_threads(nc, 64, [&](int64_t k0, int64_t k1) {
+    // the cells: storage layers in cell order, the row parts' bound terms, where they start (B) or end (A)
+    // for the links, and the programs, equal ones once (by hash, then compared). Each thread keeps the
+    // first program of each hash in its run of cells; a cell's template is numbered among them at first.
+    struct Run {
+      int64_t k0;
+      std::vector<CellProg> prog;
+    };
+    std::vector<Run> runs;
+    std::mutex mu;
+    std::vector<int32_t> tmpl(size_t(nc), -1);
+    on_threads(nc, share, [&](int64_t k0, int64_t k1) {
       CellProg C;
-      std::vector<int32_t> lay;
+      Run run{k0, {}};
+      std::unordered_multimap<uint64_t, int32_t> by_hash;
       for (int64_t k = k0; k < k1; ++k) {
-        B.build(vars.data() + vp[size_t(k)], nvars(k), C, &lay);
-        differs[size_t(k)] = !C.same(prog[size_t(tmpl[size_t(k)])]);
-        std::copy(lay.begin(), lay.end(), S.layer.begin() + lbase[size_t(k)]);
+        int32_t *lay = S.layer.data() + lbase[size_t(k)];
+        if (!B.build(vars.data() + vp[size_t(k)], nvars(k), C, lay)) {
+          ok = false;
+          return;
+        }
+        if (!C.pairs) all_pairs = false;
+        const uint64_t h = C.hash();
+        int32_t t = -1;
+        const auto eq = by_hash.equal_range(h);
+        for (auto it = eq.first; it != eq.second && t < 0; ++it)
+          if (C.same(run.prog[size_t(it->second)])) t = it->second;
+        if (t < 0) {
+          t = int32_t(run.prog.size());
+          run.prog.push_back(C);
+          by_hash.emplace(h, t);
+        }
+        tmpl[size_t(k)] = t;
         for (size_t q = 0; q < C.row.size(); ++q) {
           const int32_t Lb = lay[C.row[q] & 0x1FFFu], Le = lay[(C.row[q] >> 13) & 0x1FFFu];
           const int64_t r = rbase[size_t(k)] + int64_t(q);
@@ -601,9 +631,34 @@ bool build_cells(Plan &P, const std::vector<int64_t> &iptr, const std::vector<in
           else part_of[size_t(Le)] = int32_t(r);
         }
       }
+      std::lock_guard<std::mutex> lk(mu);
+      runs.push_back(std::move(run));
     });
-    for (int32_t k = 0; k < nc; ++k)
-      if (differs[size_t(k)]) append(k);
+    if (!ok) return false;
+    // the runs' programs in one list, in the order of their first cells
+    std::sort(runs.begin(), runs.end(), [](const Run &a, const Run &b) { return a.k0 < b.k0; });
+    std::vector<CellProg> prog;
+    {
+      std::unordered_multimap<uint64_t, int32_t> by_hash;
+      for (size_t q = 0; q < runs.size(); ++q) {
+        std::vector<int32_t> to;
+        for (CellProg &C : runs[q].prog) {
+          const uint64_t h = C.hash();
+          int32_t t = -1;
+          const auto eq = by_hash.equal_range(h);
+          for (auto it = eq.first; it != eq.second && t < 0; ++it)
+            if (C.same(prog[size_t(it->second)])) t = it->second;
+          if (t < 0) {
+            t = int32_t(prog.size());
+            prog.push_back(std::move(C));
+            by_hash.emplace(h, t);
+          }
+          to.push_back(t);
+        }
+        const int64_t k1 = q + 1 < runs.size() ? runs[q + 1].k0 : nc;
+        for (int64_t k = runs[q].k0; k < k1; ++k) tmpl[size_t(k)] = to[size_t(tmpl[size_t(k)])];
+      }
+    }
     auto lds = [&](int32_t kind) {
       int32_t most = 0;
       for (const CellProg &C : prog) most = std::max(most, cell_lds(C.nl, int32_t(C.row.size()), C.xa, kind, S.block));
