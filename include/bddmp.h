@@ -266,6 +266,23 @@ int32_t bddmp_plan_export_wave_split(const bddmp_plan *plan, int32_t pass, int32
  */
 int32_t bddmp_plan_digest(const bddmp_plan *plan, uint64_t *digest);
 
+/* The plan's cells: what iterate runs in the default launch form (bddmp_solver_set_graphs). */
+typedef struct {
+  int32_t kind;        /* 0: none (one launch per wave, replayed), 1: every component in one workgroup,
+                          2: two stages, A (the beginning of each instance's order) and B             */
+  int32_t n_cells[2];  /* workgroups of stages A and B (all in B for kind 1)                           */
+  int32_t form[2];     /* 0: a narrow layer per lane, 1: levels of up to four nodes, 2: a variable in
+                          two rows per lane                                                            */
+  int32_t lanes[2];    /* lanes of a workgroup                                                         */
+  int32_t lds[2];      /* bytes of LDS of a workgroup                                                  */
+} bddmp_cells;
+
+/*
+ * *out = the plan's cells. A solver on a device whose workgroups have less LDS than a stage's runs wave
+ * launches all the same. INVALID_ARG for a null plan or out.
+ */
+int32_t bddmp_plan_cells(const bddmp_plan *plan, bddmp_cells *out);
+
 /* Forward and backward wave of every variable (1-based, 0 for variables in no row); host [n_vars]. */
 int32_t bddmp_plan_export_waves(const bddmp_plan *plan, int32_t *wave_fwd, int32_t *wave_bwd);
 

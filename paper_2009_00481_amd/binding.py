@@ -62,6 +62,11 @@ class KernelTimes(C.Structure):
         return {k: getattr(self, k) for k, _ in self._fields_}
 
 
+class Cells(C.Structure):
+    _fields_ = [("kind", C.c_int32), ("n_cells", C.c_int32 * 2), ("form", C.c_int32 * 2), ("lanes", C.c_int32 * 2),
+                ("lds", C.c_int32 * 2)]
+
+
 # every symbol the header declares, with (restype, argtypes)
 _P, _I32, _I64, _D = C.c_void_p, C.c_int32, C.c_int64, C.c_double
 SIGNATURES = {
@@ -82,6 +87,7 @@ SIGNATURES = {
     "bddmp_plan_export_structure": (_I32, [_P, _P, _P, _P, _P]),
     "bddmp_plan_export_waves": (_I32, [_P, _P, _P]),
     "bddmp_plan_digest": (_I32, [_P, _P]),
+    "bddmp_plan_cells": (_I32, [_P, C.POINTER(Cells)]),
     "bddmp_plan_export_tile_deps": (_I32, [_P, _I32, _P, _P, _P]),
     "bddmp_plan_export_wave_split": (_I32, [_P, _I32, _P, _P, _P]),
     "bddmp_solver_bind": (_I32, [_P, _P, C.c_size_t, _P, C.POINTER(_P)]),
@@ -277,6 +283,12 @@ def bddmp_plan_export_waves(plan, n: int):
     b = np.zeros(max(n, 1), np.int32)
     _check(lib().bddmp_plan_export_waves(plan, _ptr(f), _ptr(b)))
     return f[:n], b[:n]
+
+
+def bddmp_plan_cells(plan) -> Cells:
+    out = Cells()
+    _check(lib().bddmp_plan_cells(plan, C.byref(out)))
+    return out
 
 
 def bddmp_plan_digest(plan) -> int:
@@ -515,6 +527,12 @@ class Plan:
     def digest(self) -> int:
         """64-bit digest of every array the plan uploads and of its layout sizes."""
         return bddmp_plan_digest(self.h)
+
+    def cells(self) -> dict:
+        """The cells that iterate runs in the default launch form: kind (0: none), and per stage (A, B) the
+        number of cells, their form, lanes and bytes of LDS."""
+        c = bddmp_plan_cells(self.h)
+        return {k: getattr(c, k) if k == "kind" else tuple(getattr(c, k)) for k, _ in Cells._fields_}
 
     def tile_deps(self, pass_: int):
         """(dep_ptr, dep_list, tile_group) of the dataflow launch's tiles in pass 0 (forward) or 1 (backward)."""

@@ -357,6 +357,22 @@ int32_t bddmp_plan_export_wave_split(const bddmp_plan *h, int32_t pass, int32_t 
   return BDDMP_OK;
 }
 
+int32_t bddmp_plan_cells(const bddmp_plan *h, bddmp_cells *out) {
+  if (!h || !out) return set_error(BDDMP_INVALID_ARG, "null plan or out");
+  const bddmp::Plan &P = h->plan;
+  *out = bddmp_cells{};
+  out->kind = P.cell_kind;
+  if (P.cell_kind)
+    for (int q = 0; q < 2; ++q) {
+      const bddmp::CellStage &c = P.cell[q];
+      out->n_cells[q] = c.n_cells;
+      out->form[q] = c.kind;
+      out->lanes[q] = c.n_cells ? c.block : 0;
+      out->lds[q] = c.lds;
+    }
+  return BDDMP_OK;
+}
+
 int32_t bddmp_plan_digest(const bddmp_plan *h, uint64_t *digest) {
   if (!h || !digest) return set_error(BDDMP_INVALID_ARG, "null plan or digest");
   const bddmp::Plan &P = h->plan;

@@ -35,3 +35,36 @@ def test_cells_cost_a_plan_little_time():
         if ratio[-1] < 1.12:
             return
     assert False, ratio
+
+
+# stage forms (narrow layers, up to four nodes, two-row variables) and kind of the plans that the GPU tests
+# of the cells run, so that those tests fail to cover a form only with this one
+FORMS = {
+    "one_row": (1, 0, 64), "potts1x2_L2": (1, 2, 64), "potts5x7_L3": (1, 0, 512), "potts16x16_L4": (2, 2, 64),
+    "potts33x17_L2": (2, 2, 64), "potts40x31_L7": (2, 2, 64), "potts12x9_L16": (2, 2, 64), "star16": (1, 1, 64),
+    "star17": (1, 0, 64), "star64": (1, 0, 64), "wide4": (1, 1, 64), "wide4_long": (1, 1, 64), "wide12": (0, 0, 0),
+    "tracking200": (1, 0, 64), "tracking1400": (1, 1, 256), "tracking1800": (2, 1, 128), "tracking_batch": (1, 1, 256),
+    "potts_and_tracking": (2, 1, 512),
+}
+
+
+@pytest.mark.parametrize("name", sorted(FORMS))
+def test_cell_forms_of_the_gpu_cases(name):
+    from test_gpu_cells import CASES
+
+    assert set(FORMS) == set(CASES)
+    probs = [B.Problem.from_ilp(q) for q in CASES[name]()]
+    c = B.Plan(probs if len(probs) > 1 else probs[0], hist_cap=64).cells()
+    kind, form, lanes = FORMS[name]
+    assert (c["kind"], c["form"][1], c["lanes"][1]) == (kind, form, lanes)
+    assert (c["n_cells"][0] > 0) == (kind == 2) and (c["n_cells"][1] > 0) == (kind > 0)
+    assert all(q <= 160 << 10 for q in c["lds"])
+
+
+def test_plans_without_cells_say_so():
+    """Splits, levels of more than four nodes and variables in more than 64 rows have none."""
+    grid = B.Problem.from_ilp(I.potts_grid(4, 4, 2, seed=1))
+    for plan in (B.Plan(grid, n_intervals=2), B.Plan(B.Problem.from_ilp(I.tomography(16))),
+                 B.Plan(B.Problem.from_ilp(star(65, 2, 1)))):
+        assert plan.cells() == dict(kind=0, n_cells=(0, 0), form=(0, 0), lanes=(0, 0), lds=(0, 0))
+    assert B.Plan(grid).cells()["kind"] == 1
