@@ -26,6 +26,7 @@
 
 #include "device.h"
 #include "kernels.h"
+#include "quotient.h"
 
 namespace bddmp {
 
@@ -38,8 +39,9 @@ __device__ __forceinline__ float lane_read(float v, int l) {
   return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * l, __float_as_int(v)));
 }
 
-// minimum without the quieting of signalling NaNs that fminf adds (there are no NaNs here: a level
-// whose min-marginals are both +inf is refused when the plan is built)
+// minimum without the quieting of signalling NaNs that fminf adds: messages, multipliers and their sums hold
+// none (a level whose min-marginals are both +inf is refused when the plan is built). Absent nodes may give a
+// NaN, by an addition and so a quiet one, which the minimum drops.
 __device__ __forceinline__ float vmin(float a, float b) {
   float r;
   asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -54,16 +56,6 @@ __device__ __forceinline__ float lane_before(float v) {
 // the following one (wave_shl:1)
 __device__ __forceinline__ float lane_after(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, false));
-}
-
-// s / n for a row count n, with r = 1 / n rounded: one correction of s * r by the exact remainder is the
-// correctly rounded quotient (checked for every mantissa and n <= 64) while nothing underflows or
-// overflows; the division itself elsewhere.
-__device__ __forceinline__ float over_count(float s, float n, float r) {
-  const float a = fabsf(s);
-  if (a != 0.0f && !(a >= 0x1p-100f && a <= 0x1p100f)) return s / n;
-  const float q = s * r;
-  return fmaf(fmaf(-q, n, s), r, q);
 }
 
 // A cell's LDS. X holds one message per link between a layer and its child level, in areas of pairs of

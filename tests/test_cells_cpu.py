@@ -1,5 +1,6 @@
 """Planning of the cell launches on the CPU."""
 import os
+import subprocess
 import time
 
 import numpy as np
@@ -68,3 +69,36 @@ def test_plans_without_cells_say_so():
                  B.Plan(B.Problem.from_ilp(star(65, 2, 1)))):
         assert plan.cells() == dict(kind=0, n_cells=(0, 0), form=(0, 0), lanes=(0, 0), lds=(0, 0))
     assert B.Plan(grid).cells()["kind"] == 1
+
+
+def test_quotient_by_a_row_count(tmp_path):
+    """The cells' division by a variable's number of rows is correctly rounded: every mantissa over 1 to 64,
+    both signs, at the ends of the range that takes the correction and beyond it."""
+    src = tmp_path / "q.cpp"
+    src.write_text("""
+#include <cstdio>
+#include <cstring>
+#include <initializer_list>
+#include "quotient.h"
+static int bad = 0;
+static void check(float s, float n, float r) {
+  const float a = bddmp::over_count(s, n, r), b = s / n;
+  if (std::memcmp(&a, &b, 4) && bad++ < 5) std::printf("%a / %g: %a, not %a\\n", s, n, a, b);
+}
+int main() {
+  for (int n = 1; n <= 64; ++n) {
+    const float r = 1.0f / float(n);
+    for (int m = 0; m < 1 << 23; ++m) check(std::ldexp(1.0f + m * 0x1p-23f, m & 1 ? 3 : -40), float(n), r);
+    for (int e = -149; e < 128; ++e)
+      for (int m = 0; m < 1 << 23; m += 104729)
+        for (float sign : {1.0f, -1.0f}) check(sign * std::ldexp(1.0f + m * 0x1p-23f, e), float(n), r);
+    for (float s : {0.0f, INFINITY, -INFINITY}) check(s, float(n), r);
+  }
+  return bad != 0;
+}
+""")
+    exe = str(tmp_path / "q")
+    subprocess.run(["g++", "-O2", "-mfma", "-ffp-contract=off", "-std=c++17", "-I",
+                    os.path.join(os.path.dirname(B.LIB_PATH), "csrc"), str(src), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout
