@@ -9,7 +9,8 @@ separately and not part of a step.
 value = BDD arc-updates per second = 2 * live arcs * T per step / step time (each live arc is
 relaxed and marginalised once per pass). The roofline object prices the dominant wave kernel's
 algorithmic bytes (20 per node and 8 per incidence per pass) against MI355X HBM peak, or, where the run
-used cell launches, the 8 bytes a layer that those move per iteration; cpu_baseline
+used cell launches, the 8 bytes a layer that those move per iteration, which hbm_gbps_per_iter prices too;
+cpu_baseline
 is the fp64 CPU oracle on the same instance, one thread, on a bounded sample of iterations.
 
 smoothed_vs_plain: the differentiable form (smoothed iterations with checkpoints, then the adjoint
@@ -50,7 +51,7 @@ def log(*a):
 
 KERNEL_SOURCES = ["paper_2009_00481_amd/csrc/kernels.hip", "paper_2009_00481_amd/csrc/kernels.h",
                   "paper_2009_00481_amd/csrc/device.h", "paper_2009_00481_amd/csrc/cells.hip",
-                  "paper_2009_00481_amd/csrc/cells.cpp",
+                  "paper_2009_00481_amd/csrc/cells.cpp", "paper_2009_00481_amd/csrc/quotient.h",
                   "paper_2009_00481_amd/csrc/plan.cpp", "paper_2009_00481_amd/csrc/internal.h"]
 
 
@@ -97,14 +98,14 @@ def roofline_of(kt, traffic_rec, kernel="wave_kernel"):
             "both_passes_gbs": round((kt["fwd_bytes"] + kt["bwd_bytes"]) / ((kt["fwd_ms"] + kt["bwd_ms"]) * 1e-3) / 1e9, 1)}
 
 
-def cell_roofline(n_layers: int, iter_ms: float):
-    """Cell launches: two per iteration, which together read and write every layer's multiplier once (8
-    bytes a layer; the messages stay in LDS), so their rate says how far from HBM they are bound: by
-    instruction issue and LDS round trips."""
+def cell_roofline(kind: int, n_layers: int, iter_ms: float):
+    """Cell launches: an iteration reads and writes every layer's multiplier (8 bytes a layer; the messages
+    stay in LDS) in kind launches, so the rate says how far from HBM they are bound: by instruction issue and
+    LDS round trips. Plans of kind 1 run many iterations a launch and move less."""
     achieved = 8.0 * n_layers / (iter_ms * 1e-3) / 1e9
     return {"bound": "instruction issue and LDS latency", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "traffic_unit": "bytes/launch",
-            "kernel": "cell_kernel", "bytes_per_launch": 4.0 * n_layers, "avg_launch_us": iter_ms * 1e3 / 2}
+            "kernel": "cell_kernel", "bytes_per_launch": 8.0 * n_layers / kind, "avg_launch_us": iter_ms * 1e3 / kind}
 
 
 def oracle_bounds(workload: str, T: int):
@@ -507,12 +508,14 @@ def main():
     gbps_iter = iter_bytes / (iter_ms * 1e-3) / 1e9 if iter_ms > 0 else None
 
     roofline = roofline_of(kt, committed_traffic(args.workload, tprefix), kname)
-    # the pass times above are the wave kernels'; an iteration well below them ran as cell launches
+    # the pass times above are the wave kernels'; the default form's iterations run as cells where the plan
+    # has them, and move 8 bytes a layer
     wave_roofline = None
-    step_iter_ms = ms_per_step / T
-    cells = launch == "waves" and step_iter_ms < 0.8 * (kt["fwd_ms"] + kt["bwd_ms"]) / args.profile_iters
+    cells = launch == "waves" and plan.cells()["kind"] != 0
     if cells:
-        wave_roofline, roofline = roofline, cell_roofline(int(st.n_incidences), step_iter_ms)
+        wave_roofline, roofline = roofline, cell_roofline(plan.cells()["kind"], int(st.n_incidences), iter_ms)
+        iter_bytes = 8.0 * st.n_incidences
+        gbps_iter = iter_bytes / (iter_ms * 1e-3) / 1e9 if iter_ms > 0 else None
 
     # time to bound: first t with LB_t >= LB* - 1e-4 max(|LB*|, 1). LB* is the fp64 oracle's LB_T on
     # the same instance when it is stored for T iterations, else this run's own LB_T. Measured with
