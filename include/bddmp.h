@@ -270,6 +270,7 @@ int32_t bddmp_plan_digest(const bddmp_plan *plan, uint64_t *digest);
 typedef struct {
   int32_t kind;        /* 0: none (one launch per wave, replayed), 1: every component in one workgroup,
                           2: two stages, A (the beginning of each instance's order) and B             */
+  int32_t from;        /* calls of fewer iterations run without (what a call adds as cells is more)   */
   int32_t n_cells[2];  /* workgroups of stages A and B (all in B for kind 1)                           */
   int32_t form[2];     /* 0: a narrow layer per lane, 1: levels of up to four nodes, 2: a variable in
                           two rows per lane                                                            */
@@ -444,7 +445,7 @@ int32_t bddmp_solver_set_costs(bddmp_solver *s, const double *cost_dev);
  * with the launch that also runs the next iteration's first forward wave, and once an iteration that
  * ends with the plain last backward wave: between calls the state is always that after whole
  * iterations. Where the plan's components fit a workgroup's LDS (the grid MRFs, tracking instances,
- * small problems), the iterations run as cell launches instead of replays: one or two launches per
+ * small problems) and that is estimated to take less time (bddmp_plan_cells), the iterations run as cell launches instead of replays: one or two launches per
  * iteration, or many iterations per launch. enable = 0: every wave is launched from the host. All give
  * bitwise the same results.
  */

@@ -63,7 +63,7 @@ class KernelTimes(C.Structure):
 
 
 class Cells(C.Structure):
-    _fields_ = [("kind", C.c_int32), ("n_cells", C.c_int32 * 2), ("form", C.c_int32 * 2), ("lanes", C.c_int32 * 2),
+    _fields_ = [("kind", C.c_int32), ("from_", C.c_int32), ("n_cells", C.c_int32 * 2), ("form", C.c_int32 * 2), ("lanes", C.c_int32 * 2),
                 ("lds", C.c_int32 * 2)]
 
 
@@ -529,10 +529,10 @@ class Plan:
         return bddmp_plan_digest(self.h)
 
     def cells(self) -> dict:
-        """The cells that iterate runs in the default launch form: kind (0: none), and per stage (A, B) the
-        number of cells, their form, lanes and bytes of LDS."""
+        """The cells that iterate runs in the default launch form: kind (0: none), from_ (calls of fewer
+        iterations run without), and per stage (A, B) the number of cells, their form, lanes and bytes of LDS."""
         c = bddmp_plan_cells(self.h)
-        return {k: getattr(c, k) if k == "kind" else tuple(getattr(c, k)) for k, _ in Cells._fields_}
+        return {k: getattr(c, k) if k in ("kind", "from_") else tuple(getattr(c, k)) for k, _ in Cells._fields_}
 
     def tile_deps(self, pass_: int):
         """(dep_ptr, dep_list, tile_group) of the dataflow launch's tiles in pass 0 (forward) or 1 (backward)."""

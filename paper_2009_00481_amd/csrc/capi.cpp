@@ -362,6 +362,7 @@ int32_t bddmp_plan_cells(const bddmp_plan *h, bddmp_cells *out) {
   const bddmp::Plan &P = h->plan;
   *out = bddmp_cells{};
   out->kind = P.cell_kind;
+  out->from = P.cell_from;
   if (P.cell_kind)
     for (int q = 0; q < 2; ++q) {
       const bddmp::CellStage &c = P.cell[q];

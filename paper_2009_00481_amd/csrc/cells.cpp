@@ -721,6 +721,43 @@ bool build_cells(Plan &P, const std::vector<int64_t> &iptr, const std::vector<in
   return true;
 }
 
+// Estimated time of an iteration as cells, in us (fitted to the measurements at cells_pay in plan.cpp). Per
+// stage, the cells beyond those that the compute units hold at once (by LDS and by wavefronts) run in
+// further rounds, each as long as the largest cell's chunks and rows take in sequence (0.35 us each for a
+// wavefront by itself, 0.6 us for several, which meet at barriers, 0.15 us more on levels of up to four
+// nodes); many small cells are bound by the chunks that all wavefronts issue. Two stages add their launches,
+// the multipliers, and the cache lines of the messages that a cell hands on to scattered places.
+double cell_time(const Plan &P) {
+  double us = 1.0;
+  for (const CellStage &S : P.cell) {
+    if (!S.n_cells) continue;
+    const int32_t step = (S.n_cells + kCellSample - 1) / kCellSample;
+    double chunks = 0.0, lines = 0.0, links = 0.0, layers = 0.0;
+    int32_t most = 0, rows = 0;
+    std::vector<int32_t> line;
+    for (int32_t k = 0; k < S.n_cells; ++k) {
+      const int32_t *r = &S.rec[12 * size_t(k)];
+      layers += r[0];
+      chunks += r[1];
+      most = std::max(most, r[1]);
+      rows = std::max(rows, (r[8] + S.block - 1) / S.block);
+      if (k % step) continue;
+      line.clear();
+      for (int32_t q = 0; q < r[8]; ++q)
+        if (const int32_t to = S.link[size_t(r[5] + q)]; to >= 0) line.push_back(int32_t(int64_t(to) * S.bw / 16));
+      std::sort(line.begin(), line.end());
+      links += step * double(line.size());
+      lines += step * double(std::unique(line.begin(), line.end()) - line.begin());
+    }
+    const int32_t slots = 256 * std::min(kCellLdsCap / std::max(S.lds, 1), 2048 / S.block);
+    const double unit = (S.block == 64 ? 0.35 : 0.6) + (S.kind == kCellGen ? 0.15 : 0.0);
+    const double chain = (2.0 * most + 2.0 * rows + 2.0) * unit * ((S.n_cells + slots - 1) / slots);
+    us += std::max(chain, 0.15 / 1024.0 * 2.0 * chunks * (S.block / 64));
+    if (P.cell_kind == 2) us += 2.5 + 1e-6 * layers + 17e-6 * std::max(0.0, lines - links * S.bw / 16);
+  }
+  return us;
+}
+
 // Checks every index the cell kernels use, and that the cells run each layer exactly once, after its
 // row's previous level. Empty when sound.
 std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, const std::vector<int32_t> &childw) {

@@ -95,6 +95,7 @@ constexpr int kCellLayers = 0, kCellGen = 1, kCellPair = 2;
 // cell, bytes of LDS of a component (estimate) and of a cell
 constexpr int kCellMaxRows = 64, kCellMaxWidth = 4, kCellMaxLayers = 8188;
 constexpr int kCellLdsMax = 140 << 10, kCellLdsCap = 160 << 10;
+constexpr int kCellSample = 2048;  // cells whose boundary links are looked at for the estimate of their time
 
 // Records bddmp_last_error's message and returns code.
 int32_t set_error(int32_t code, const std::string &msg);
@@ -293,6 +294,8 @@ struct Plan {
   // cell launches (cells.cpp): 0 none; 1 every instance component in one workgroup; 2 two stages
   // (A = a prefix of each instance's order, B = the rest)
   int32_t cell_kind = 0, n_comp = 0;
+  int32_t cell_from = 0;           // fewest iterations of a call that run as cells
+  double cell_us = 0.0;            // estimated time of an iteration as cells
   std::vector<uint8_t> var_stage;  // [n] 0 = A, 1 = B
   std::vector<int32_t> var_comp;   // [n] component of the variable in its stage, -1 without rows
   CellStage cell[2];
@@ -309,6 +312,7 @@ void choose_cells(const Problem &p, Plan &P, const std::vector<int64_t> &iptr, c
                   const std::vector<int32_t> &inc_row);
 bool build_cells(Plan &P, const std::vector<int64_t> &iptr, const std::vector<int32_t> &ilist,
                  const std::vector<int32_t> &inc_row, const std::vector<int32_t> &ownw, const std::vector<int32_t> &childw);
+double cell_time(const Plan &P);
 std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, const std::vector<int32_t> &childw);
 void greedy_colour_order(const Problem &p, std::vector<int32_t> &order);
 

@@ -16,6 +16,7 @@
 // therefore one contiguous segment, and each wave is one contiguous layer range. Node arrays
 // follow the layer order. Arcs are packed as two 16-bit child codes per node.
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <exception>
 #include <thread>
@@ -648,6 +649,28 @@ static bool rows_pay(const Plan &P) {
   return double(P.I) <= 78e3 * P.Df || extra_lines(P) <= 78e3 * P.Df;
 }
 
+// Fewest iterations of a call that run as cells, 0 if none: where they are estimated to take less than a
+// launch per wave replayed as a graph. A replay takes 6 us, a wave 5.5 (10 with general levels), a million
+// layers 10 (14 beyond the eight million whose messages the last-level cache holds), a million nodes of plans
+// with general levels 10 more. A call as cells takes 8 us more, and 6.5 a million layers, to gather the
+// multipliers into the cells and back. Measured, us per iteration as waves / as cells in calls of 50, and of 1:
+//   Potts 8x8x3 36 / 10 (39 / 20), 128x128x4 61 / 28 (65 / 52), 256x256x8 366 / 166 (372 / 332), 128x128x2 29 / 23
+//     (32 / 38), 600x600x2 135 / 127 (149 / 224); 32 tracking instances 916 / 132 (916 / 154)
+//   random pairs of variables, one component of 4600 layers in a workgroup 18 / 18 (26 / 30), 64 of them 18 /
+//     21 (25 / 34), 1500 68 / 131 (86 / 181); 1500 of 1000 layers 29 / 18 (36 / 35); in two stages, 0.2 million
+//     layers 19 / 23 (25 / 34), 4 million 65 / 85 (79 / 121)
+//   random rows of three, 1500 components of 5100 layers 89 / 140 (105 / 202), one 25 / 21 (28 / 33); of eight,
+//     1500 of 4800 layers 131 / 142 (137 / 201), one 52 / 22 (55 / 34), with levels of up to four nodes 443 / 205
+//     (450 / 375) and 110 / 28 (115 / 44)
+// Of 54 such plans the estimates choose the slower form of two, by 3%.
+static int32_t cells_pay(const Plan &P) {
+  double wave = 6.0 + 10e-6 * double(P.I) + 4e-6 * std::max(0.0, double(P.I) - 8e6);
+  for (const WaveRange &w : P.fwd_waves) wave += w.narrow_only ? 5.5 : 10.0;
+  if (P.n_general) wave += 10e-6 * double(P.N);
+  const double gain = wave - P.cell_us, once = 8.0 + 6.5e-6 * double(P.I);
+  return gain > 0.0 && once < 1e6 * gain ? std::max(1, int32_t(std::ceil(once / gain))) : 0;
+}
+
 int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
   P = Plan{};
   const int32_t n = p.n;
@@ -879,8 +902,7 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
   }
 
   // the cells are planned beside the storage order, the tiles and their checks, which take longer: one after
-  // the other, cells made a plan of Potts 128x128x4 take 405 ms instead of 318 (small plans choose theirs
-  // in less time than a thread takes to start)
+  // the other, cells made a plan of Potts 128x128x4 take 405 ms instead of 318
   Beside choosing;
   if (I < 1 << 14) choose_cells(p, P, iptr, ilist, inc_row);
   else choosing.run([&] { choose_cells(p, P, iptr, ilist, inc_row); });
@@ -1107,6 +1129,7 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
     cells.run([&] {
       if (build_cells(P, iptr, ilist, inc_row, ownw, childw)) {
         cells_bad = validate_cells(P, ownw, childw);
+        P.cell_us = cell_time(P);
       } else {
         P.cell_kind = 0;
         P.cell[0] = P.cell[1] = CellStage{};
@@ -1503,6 +1526,11 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
   cells.join();
   if (!bad.empty() || !cells_bad.empty())
     return set_error(BDDMP_INVALID_ARG, "internal layout check failed: " + (bad.empty() ? cells_bad : bad));
+  P.cell_from = P.cell_kind ? cells_pay(P) : 0;
+  if (P.cell_kind && !P.cell_from) {
+    P.cell_kind = 0;
+    P.cell[0] = P.cell[1] = CellStage{};
+  }
 
   // arena layout
   ArenaLayout &A = P.lay;

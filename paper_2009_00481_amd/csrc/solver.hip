@@ -616,7 +616,7 @@ int32_t solver_iterate(Solver &S, int32_t n) {
   if (n < 0) return set_error(BDDMP_INVALID_ARG, "negative iteration count");
   if (S.use_graph && n > 0) {
     const Plan &P = *S.plan;
-    if (cell_kind(S)) return cell_iterations(S, n);
+    if (cell_kind(S) && n >= P.cell_from) return cell_iterations(S, n);
     const bool wrap = use_wrap(S);
     if (!S.gexec || (wrap && !S.gexec_wrap) || S.graph_gsel != S.D.gsel)
       if (int32_t rc = capture_iteration(S)) return rc;

@@ -67,7 +67,7 @@ def test_plans_without_cells_say_so():
     grid = B.Problem.from_ilp(I.potts_grid(4, 4, 2, seed=1))
     for plan in (B.Plan(grid, n_intervals=2), B.Plan(B.Problem.from_ilp(I.tomography(16))),
                  B.Plan(B.Problem.from_ilp(star(65, 2, 1)))):
-        assert plan.cells() == dict(kind=0, n_cells=(0, 0), form=(0, 0), lanes=(0, 0), lds=(0, 0))
+        assert plan.cells() == dict(kind=0, from_=0, n_cells=(0, 0), form=(0, 0), lanes=(0, 0), lds=(0, 0))
     assert B.Plan(grid).cells()["kind"] == 1
 
 
@@ -102,3 +102,34 @@ int main() {
                     os.path.join(os.path.dirname(B.LIB_PATH), "csrc"), str(src), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout
+
+
+def random_rows(n, m, k, cmax=1, rhs=1, seed=1):
+    """m rows of k variables, one from each of k blocks of the order."""
+    r = np.random.default_rng([n, m, k, seed])
+    col = (r.integers(0, n // k, (m, k)) + np.arange(k) * (n // k)).reshape(-1)
+    coef = r.integers(1, cmax + 1, (16, k))[r.integers(0, 16, m)].reshape(-1)
+    return I.ILP(n, r.standard_normal(n), np.arange(m + 1) * k, col.astype(np.int32), coef, np.ones(m, np.int8),
+                 np.full(m, rhs, np.int64), None)
+
+
+@pytest.mark.parametrize("make,count,kind,short", [
+    # one component of many layers in few steps keeps a compute unit busy alone
+    (lambda s: random_rows(900, 2300, 2, seed=s), 40, 0, False),
+    (lambda s: random_rows(1500, 1700, 3, 2, 3, seed=s), 300, 0, False),
+    (lambda s: random_rows(1500, 1700, 3, 2, 3, seed=s), 1, 1, True),
+    (lambda s: random_rows(1600, 600, 8, seed=s), 1, 1, False),
+    (lambda s: random_rows(1600, 600, 8, 2, 3, seed=s), 64, 1, False),
+    # two stages that hand every message on to another place
+    (lambda s: random_rows(100000, 100000, 2, seed=s), 1, 0, False),
+    (lambda s: I.potts_grid(300, 300, 2, seed=s), 1, 2, True),
+    (lambda s: I.potts_grid(128, 128, 4, seed=s), 1, 2, False),
+    (lambda s: I.tracking(300, seed=s), 8, 1, False),
+])
+def test_cells_run_where_they_take_less_time(make, count, kind, short):
+    """Few large components of few steps, and scattered boundaries, took up to 1.9 times as long as cells; calls
+    of few iterations pay for gathering the multipliers."""
+    q = [B.Problem.from_ilp(p, order=p.order is not None) for p in (make(s) for s in range(count))]
+    c = B.Plan(q if count > 1 else q[0], hist_cap=64).cells()
+    assert c["kind"] == kind
+    assert (c["from_"] > 1) == short and (c["from_"] > 0) == (kind > 0)

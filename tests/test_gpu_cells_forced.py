@@ -112,3 +112,20 @@ def test_forced_rows_in_cells_bitwise(name):
         assert np.array_equal(got.astype(np.float64), np.asarray(want, np.float64))
     # (the variables of these rows are forced: differences are infinite)
     assert np.isinf(r1 - r0).any()
+
+
+def test_short_calls_between_cells_bitwise():
+    """Calls of fewer iterations than cells take run as replayed waves: any sequence gives the same."""
+    plan = B.Plan(B.Problem.from_ilp(I.potts_grid(300, 300, 2, seed=1)), hist_cap=64)
+    k = plan.cells()["from_"]
+    assert plan.cells()["kind"] == 2 and k > 1
+    out = []
+    for graphs in (True, False):
+        s = B.Solver(plan)
+        s.set_graphs(graphs)
+        for n in (1, k, 1, k - 1, k + 9, 1):
+            s.iterate(n)
+        m0, m1 = s.min_marginals()
+        out.append([v.cpu().numpy() for v in (s.get_lambda(), m0, m1)] + [s.lb_history(64)])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)

@@ -118,3 +118,20 @@ for name in (a, b):
     print(*(sum(k in q for q in name) for k in ("wave_kernel", "row_")))
 """).split()
     assert [int(v) > 0 for v in out] == [not rows, rows] * 2
+
+
+def test_short_calls_run_without_cells(stub):
+    """Where gathering the multipliers costs more than a few iterations gain, short calls are replays."""
+    out = hip_stub.run(stub, """
+plan = B.Plan(B.Problem.from_ilp(I.potts_grid(300, 300, 2, seed=1)))
+k = plan.cells()["from_"]
+h = bind(plan)
+print(k)
+for n in (1, k - 1, k, k + 1, 1):
+    launches()
+    B.bddmp_solver_iterate(h, n)
+    names = launches()
+    print(*(sum(q in x for x in names) > 0 for q in ("cell_kernel", "wave_kernel")))
+""").splitlines()
+    assert int(out[0]) > 1
+    assert out[1:] == ["False True", "False True", "True False", "True False", "False True"]
