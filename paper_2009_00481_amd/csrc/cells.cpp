@@ -94,6 +94,11 @@ void on_threads(int64_t n, int64_t min_chunk, F &&f) {
   if (err) std::rethrow_exception(err);
 }
 
+// cells to a host thread, at least: some 16384 layers, however large the cells
+int64_t cell_share(int64_t cells, int64_t layers) {
+  return std::max<int64_t>(1, cells * 16384 / std::max<int64_t>(layers, 1));
+}
+
 }  // namespace
 
 // Chooses the stages: per instance the cut of its processing order that makes A's and B's largest
@@ -559,8 +564,7 @@ bool build_cells(Plan &P, const std::vector<int64_t> &iptr, const std::vector<in
     // sizes of the cells, and where each one's layers and row parts start
     std::vector<int64_t> lbase(size_t(nc) + 1, 0), rbase(size_t(nc) + 1, 0);
     std::atomic<bool> ok{true}, all_pairs{true};
-    // cells to a host thread: about as many layers in all, however large the cells
-    const int64_t share = std::max<int64_t>(1, int64_t(nc) * 16384 / std::max<int64_t>(total, 1));
+    const int64_t share = cell_share(nc, total);
     on_threads(nc, share, [&](int64_t k0, int64_t k1) {
       std::vector<int32_t> at, by;
       for (int64_t k = k0; k < k1; ++k) {
@@ -777,7 +781,8 @@ std::string validate_cells(const Plan &P, const std::vector<int32_t> &ownw, cons
         if (S.layer[q] >= P.I) return "cell layer";
         place[size_t(S.layer[q])] = int32_t(q);
       }
-    on_threads(S.n_cells, 16, [&](int64_t k0, int64_t k1) {
+    const int64_t share = cell_share(S.n_cells, int64_t(S.layer.size()));
+    on_threads(S.n_cells, share, [&](int64_t k0, int64_t k1) {
       auto fail = [&](const char *w) { bad = w; };
       std::vector<int32_t> step_of, part_f, part_b, chunk_of, chunk0;
       std::vector<std::pair<int32_t, int32_t>> wide;

@@ -904,8 +904,7 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
   // the cells are planned beside the storage order, the tiles and their checks, which take longer: one after
   // the other, cells made a plan of Potts 128x128x4 take 405 ms instead of 318
   Beside choosing;
-  if (I < 1 << 14) choose_cells(p, P, iptr, ilist, inc_row);
-  else choosing.run([&] { choose_cells(p, P, iptr, ilist, inc_row); });
+  choosing.run([&] { choose_cells(p, P, iptr, ilist, inc_row); });
 
   // Storage order. Each forward wave sorts its variables by group of instances, then by backward wave, then by the storage
   // position of their earliest parent layer (the previous level of one of their rows), ties and
