@@ -511,7 +511,7 @@ def main():
     # the pass times above are the wave kernels'; the default form's iterations run as cells where the plan
     # has them, and move 8 bytes a layer
     wave_roofline = None
-    cells = launch == "waves" and plan.cells()["kind"] != 0
+    cells = launch == "waves" and plan.cells()["kind"] != 0 and T >= plan.cells()["from_"]
     if cells:
         wave_roofline, roofline = roofline, cell_roofline(plan.cells()["kind"], int(st.n_incidences), iter_ms)
         iter_bytes = 8.0 * st.n_incidences
