@@ -101,7 +101,8 @@ def roofline_of(kt, traffic_rec, kernel="wave_kernel"):
 def cell_roofline(kind: int, n_layers: int, iter_ms: float):
     """Cell launches: an iteration reads and writes every layer's multiplier (8 bytes a layer; the messages
     stay in LDS) in kind launches, so the rate says how far from HBM they are bound: by instruction issue and
-    LDS round trips. Plans of kind 1 run many iterations a launch and move less."""
+    LDS round trips. iter_ms: a step's time over its iterations (short calls, as in the kernel times, gather
+    the multipliers more often). Plans of kind 1 run many iterations a launch and move less."""
     achieved = 8.0 * n_layers / (iter_ms * 1e-3) / 1e9
     return {"bound": "instruction issue and LDS latency", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "traffic_unit": "bytes/launch",
@@ -513,7 +514,7 @@ def main():
     wave_roofline = None
     cells = launch == "waves" and plan.cells()["kind"] != 0 and T >= plan.cells()["from_"]
     if cells:
-        wave_roofline, roofline = roofline, cell_roofline(plan.cells()["kind"], int(st.n_incidences), iter_ms)
+        wave_roofline, roofline = roofline, cell_roofline(plan.cells()["kind"], int(st.n_incidences), ms_per_step / T)
         iter_bytes = 8.0 * st.n_incidences
         gbps_iter = iter_bytes / (iter_ms * 1e-3) / 1e9 if iter_ms > 0 else None
 
