@@ -231,11 +231,18 @@ namespace {
 //
 // Small components go to one-wavefront cells, whose steps need no barrier. Cells of two-row variables
 // (one lane each) hold up to 1024 layers, others (one lane per layer) up to 256: a step then fills about
-// one wavefront on the grid workloads, and ten or more cells fit a compute unit's LDS. Measured on Potts
-// 256x256x8, us per iteration: 168 with 1024 / 256, 173 with 1024 / 512, 179 with 512 / 512, 198 with 2048
-// layers on two wavefronts. Plans of few cells share the layers out so that every compute unit gets two.
+// one wavefront on the grid workloads, and ten or more cells fit a compute unit's LDS. Measured, us per
+// iteration with pairs of 512 / 1024 / 2048: Potts 256x256x8 165 / 168 / 233, 128x128x4 25 / 28 / 36, 300x300x4
+// 65 / 75 / 99, 40x40x16 57 / 52 / 54 (512 would be the better line for up to eight labels); others of 128 / 256
+// / 512: Potts 256x256x8 181 / 168 / 174, 128x128x4 28 / 28 / 39, a million layers of random pairs 9 / 11 / 15,
+// of disjoint rows of ten 22 / 13 / 11. Plans of few cells share the layers out so that every compute unit
+// gets two, down to 64 layers: total / 256, / 512, / 1024 on 64x64x4 24.3, 20.0, 19.1, on 32x32x8 29.2, 28.3,
+// 28.6; at least 32, 64, 128, 256 layers on 16x16x4 16.1, 15.8, 16.6, 18.1.
+//
 // A larger component is a cell by itself, on the fewest lanes that take at most a quarter more chunks
-// than 512 lanes would.
+// than 512 lanes would: 64, 128, 256, 512 lanes on Potts 8x8x3 45, 26, 16, 10.5, on a component of eight steps
+// of 600 layers 94, 52, 33, 22; 256 are taken for a tracking instance of 1400 detections, 148, 93, 80, 73, and
+// for 5x5x2 9.9, 6.9, 5.2, 5.1 (512 would gain up to 9% there).
 void cell_shape(int32_t big, int64_t total, const std::vector<int32_t> &largest, bool pairs, int32_t &block, int32_t &room) {
   const int32_t most = pairs ? 1024 : 256;
   if (big <= most) {
