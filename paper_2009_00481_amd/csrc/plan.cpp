@@ -1565,7 +1565,12 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
   A.cost = take(8 * nn);
   A.var_first = take(4 * nn);
   A.var_nj = take(4 * nn);
-  A.d_fresh = take(4 * In);
+  // a run of cell launches keeps its multipliers in cell order where min-marginals leave their differences
+  // for the rounding: neither is used outside its own call
+  const size_t c_lam1 = align256(4 * P.cell[0].layer.size());
+  A.d_fresh = take(std::max(4 * In, c_lam1 + 4 * P.cell[1].layer.size()));
+  A.c_lam[0] = A.d_fresh;
+  A.c_lam[1] = A.d_fresh + c_lam1;
   A.mbuf = take(4 * nn);
   A.xbuf = take(nn);
   A.part = take(8 * 2 * size_t(kLbBlocks));
@@ -1622,7 +1627,6 @@ int32_t make_plan(const Problem &p, const bddmp_options &opt, Plan &P) {
     A.c_layer[q] = take(4 * C.layer.size());
     A.c_link[q] = take(4 * C.link.size());
     A.c_term[q] = take(4 * C.term.size());
-    A.c_lam[q] = take(4 * C.layer.size());
     A.c_in[q] = take(4 * C.link.size() * size_t(C.bw));
   }
   A.total = off;

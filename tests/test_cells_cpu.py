@@ -29,6 +29,7 @@ def test_cells_cost_a_plan_little_time():
         return time.perf_counter() - t, int(p.stats.device_bytes)
 
     assert plan(64)[1] > 1.2 * plan(65)[1]  # (the one with cells holds their arrays)
+    assert plan(64)[1] < 1.28 * plan(65)[1]  # (but no second copy of the multipliers)
     ratio = []
     for _ in range(8):
         a, b = zip(*((plan(64)[0], plan(65)[0]) for _ in range(4)))
