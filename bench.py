@@ -10,8 +10,7 @@ value = BDD arc-updates per second = 2 * live arcs * T per step / step time (eac
 relaxed and marginalised once per pass). The roofline object prices the dominant wave kernel's
 algorithmic bytes (20 per node and 8 per incidence per pass) against MI355X HBM peak, or, where the run
 used cell launches, the 8 bytes a layer that those move per iteration, which hbm_gbps_per_iter prices too;
-cpu_baseline
-is the fp64 CPU oracle on the same instance, one thread, on a bounded sample of iterations.
+cpu_baseline is the fp64 CPU oracle on the same instance, one thread, on a bounded sample of iterations.
 
 smoothed_vs_plain: the differentiable form (smoothed iterations with checkpoints, then the adjoint
 giving d LB_alpha / d c) on Potts 128x128 with 4 labels, 50 iterations, alpha in {1, 0.1, 0.01},
